@@ -42,6 +42,29 @@
 namespace ugbs {
 namespace {
 
+// Work order: two kv heads at a time across the whole device (XCDs 0-3 on
+// one, 4-7 on the other, so the memory-side cache holds the working set),
+// one kv head at a time when the (batch, kv head) count is odd; within a
+// kv head the XCDs of its group take its tiles in turn, heaviest first, the
+// sibling query heads of a tile one after another on the same XCD, whose L2
+// then serves the blocks they share.  Workgroup j runs on XCD j mod 8.
+// - Above 64 tiles the turns go back and forth over the XCDs, so that no XCD
+//   always gets the heavier tile (d 256, 64K: 4.52 -> 4.39 ms; at 64 tiles,
+//   two rounds of units, it was 1% slower).
+// - When the tiles don't divide over the XCDs of a group, an XCD has one
+//   fewer in the last turn and the workgroups of the missing one leave at
+//   once.  Dealing such lengths unit by unit over all XCDs put sibling heads
+//   on different ones: 0.70 -> 0.66 ms at 141 blocks (28/4 heads, batch 2),
+//   0.205 -> 0.188 ms at 253 blocks (16/4 heads, d 64, with the turns).
+//   Below 64 tiles that order stays: a kv head's K and V fit an L2 whole, and
+//   the padding could double the grid.
+struct AttendOrder {
+  int hpp, lg;   // kv heads in flight, log2 of the XCDs per kv head
+  int per;       // workgroups of one XCD per kv head; 0: units round-robin
+  int snake;     // the tiles change direction every turn
+  int grid;
+};
+
 struct AttnParams {
   Shape s;
   const uint16_t* Q;
@@ -50,7 +73,7 @@ struct AttnParams {
   const int32_t* kv_idx;
   uint16_t* O;
   int kv_width;
-  int n_units;
+  AttendOrder order;
   int conc;          // units resident at once on one XCD (rotation period)
   float scale_log2;
   // in-kernel selection (ugbs_attend_select)
@@ -84,6 +107,43 @@ template <int D, bool V>
 using FetchPlan = FetchPlanT<D, V, Geo<D>::NWV>;
 
 
+AttendOrder attend_order(const Shape& s) {
+  AttendOrder o;
+  const int nbh = s.B * s.Hkv;
+  o.hpp = nbh % 2 == 0 ? 2 : 1;
+  o.lg = nbh % 2 == 0 ? 2 : 3;
+  o.snake = s.T > 64 ? 1 : 0;
+  const int stride = 1 << o.lg;
+  if (s.T < 64 && s.T % stride != 0) {
+    o.per = 0;
+    o.grid = nbh * s.G * s.T;
+  } else {
+    o.per = (s.T + stride - 1) / stride * s.G;
+    o.grid = 8 * ((nbh + o.hpp - 1) / o.hpp) * o.per;
+  }
+  return o;
+}
+
+// This workgroup's unit; false: it has none.
+__device__ __forceinline__ bool attend_unit(const Shape& s, const AttendOrder& o, Unit* u) {
+  if (o.per == 0) {
+    *u = unit_of(blockIdx.x, s);
+    return true;
+  }
+  const int n_x = blockIdx.x >> 3, x = blockIdx.x & 7;
+  const int phase = n_x / o.per;
+  const int within = n_x - phase * o.per;
+  const int hh = o.hpp * phase + (x >> o.lg);                // (batch, kv head) index
+  // tile rank, heaviest first, in a snake over the XCDs of the group
+  const int turn = within / s.G, last = (1 << o.lg) - 1;
+  const int tr = (turn << o.lg) + ((x ^ ((o.snake & (turn + phase)) ? last : 0)) & last);
+  if (hh >= s.B * s.Hkv || tr >= s.T) return false;
+  u->b = hh / s.Hkv;
+  u->h = (hh % s.Hkv) * s.G + (within - turn * s.G);
+  u->t = s.T - 1 - tr;
+  return true;
+}
+
 // Two waves per SIMD at every d (at d = 256 through the four-wave geometry).
 template <int D, int MODE>
 __global__ void __launch_bounds__(Geo<D>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -104,34 +164,8 @@ attend_kernel(AttnParams P) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);  // wave index, uniform per wave
   const int g = lane >> 4, c16 = lane & 15;
-  // Work order: two kv heads at a time across the whole device (XCDs 0-3 on
-  // one, 4-7 on the other, so the memory-side cache holds the working set),
-  // one kv head at a time when the (batch, kv head) count is odd; within a
-  // kv head the XCDs of its group take its tiles round-robin (heaviest
-  // first, every tile size on every XCD), the sibling query heads of a tile
-  // one after another on the same XCD.  Workgroup j runs on XCD j mod 8.
   Unit u;
-  {
-    const int nbh = s.B * s.Hkv;
-    const int hpp = (nbh % 2 == 0 && s.T % 4 == 0) ? 2 : 1;   // kv heads in flight
-    const int stride = 8 / hpp;                                // XCDs per kv head
-    const int n_x = blockIdx.x >> 3, x = blockIdx.x & 7;
-    if (s.T % stride != 0) {                                   // fall back: units dealt round-robin to the XCDs
-      const int uid = blockIdx.x;
-      if (uid >= P.n_units) return;
-      u = unit_of(uid, s);
-    } else {
-      const int tiles_x = s.T / stride;                        // tiles per XCD and kv head
-      const int phase = n_x / (tiles_x * s.G);
-      const int within = n_x - phase * tiles_x * s.G;
-      const int hh = hpp * phase + x / stride;                 // (batch, kv head) index
-      if (hh >= nbh) return;
-      const int tr = stride * (within / s.G) + x % stride;
-      u.b = hh / s.Hkv;
-      u.h = (hh % s.Hkv) * s.G + within % s.G;
-      u.t = s.T - 1 - tr;
-    }
-  }
+  if (!attend_unit(s, P.order, &u)) return;
   const int kvh = u.h / s.G;
   const size_t rowid = ((size_t)u.b * s.H + u.h) * s.T + u.t;
 
@@ -681,7 +715,7 @@ int xcd_concurrency(size_t smem) {
 template <int D, int MODE>
 hipError_t launch_t(AttnParams P, hipStream_t stream) {
   const size_t smem = sizeof(int32_t) * (size_t)P.kv_width;
-  const int grid = ((P.n_units + 7) / 8) * 8;
+  const int grid = P.order.grid;
   if (D > 128) {  // the K and V tiles alone take 64 KB of static LDS
     const hipError_t e = hipFuncSetAttribute((const void*)attend_kernel<D, MODE>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
@@ -699,13 +733,13 @@ hipError_t launch_attend(const Shape& s, const uint16_t* Q, const uint16_t* K,
                          uint16_t* O, hipStream_t stream) {
   AttnParams P{};
   P.s = s;
+  P.order = attend_order(s);
   P.Q = Q;
   P.K = K;
   P.V = V;
   P.kv_idx = kv_idx;
   P.O = O;
   P.kv_width = kv_width;
-  P.n_units = s.B * s.H * s.T;
   P.scale_log2 = s.scale * 1.4426950408889634f;
   if (s.d == 256) return launch_t<256, kLists>(P, stream);
   return s.d == 128 ? launch_t<128, kLists>(P, stream) : launch_t<64, kLists>(P, stream);
@@ -716,13 +750,13 @@ hipError_t launch_attend_select(const Shape& s, const uint16_t* Q, const uint16_
                                 const void* workspace, uint16_t* O, hipStream_t stream) {
   AttnParams P{};
   P.s = s;
+  P.order = attend_order(s);
   P.Q = Q;
   P.K = K;
   P.V = V;
   P.O = O;
   // at most |F| + (rho k - |F|) distinct blocks per tile, and never more than t + 1
   P.kv_width = s.W < s.NB ? s.W : s.NB;
-  P.n_units = s.B * s.H * s.T;
   P.scale_log2 = s.scale * 1.4426950408889634f;
   const unsigned char* ws = static_cast<const unsigned char*>(workspace);
   P.sel_scores = scores;
@@ -741,12 +775,12 @@ hipError_t launch_attend_bitmap(const Shape& s, const uint16_t* Q, const uint16_
                                 hipStream_t stream) {
   AttnParams P{};
   P.s = s;
+  P.order = attend_order(s);
   P.Q = Q;
   P.K = K;
   P.V = V;
   P.O = O;
   P.kv_width = s.NB;  // a row may list every visible block
-  P.n_units = s.B * s.H * s.T;
   P.scale_log2 = s.scale * 1.4426950408889634f;
   P.bitmap = bitmap;
   P.nw = (s.NB + 31) / 32;
