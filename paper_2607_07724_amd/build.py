@@ -31,7 +31,7 @@ PROBE_LIB = os.path.join(PKG, "libugbs_probe.so")
 ARCH = "gfx950"
 LLVM_BIN = "/opt/rocm/lib/llvm/bin"
 
-SOURCES = ["block_meta.hip", "score_select.hip", "route.hip", "attend.hip", "rowsel.hip", "bai.hip", "quest_valu.hip", "abi.hip"]
+SOURCES = ["block_meta.hip", "score_select.hip", "route.hip", "attend.hip", "attend_keys.hip", "rowsel.hip", "bai.hip", "quest_valu.hip", "abi.hip"]
 PROBE_SOURCES = ["probe_peaks.hip"]
 
 CFLAGS = [
@@ -46,7 +46,8 @@ CFLAGS = [
 # Per-source additions.  The scoring kernels keep their MFMA accumulators in
 # VGPRs, where the tile max reads them (no accumulator-register copies); the
 # attention kernel needs the accumulator registers for its budget.
-EXTRA_FLAGS = {"score_select.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA_FLAGS = {"score_select.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+               "attend_keys.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 PACKED_FP32 = re.compile(r"\bv_pk_(add|mul|fma)_f32\b")
 
