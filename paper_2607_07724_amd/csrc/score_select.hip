@@ -30,7 +30,8 @@
 // caller's [.., N_B] score tensor or into packed rows of the workspace (row
 // (b, h, t) holds the t-1 candidates 1..t-1).
 //
-// select_kernel: one wave per unit, heaviest tile first.  Tile scores
+// select_kernel: one wave per unit, heaviest tile first; compiled for five row
+// sizes, and slots past a row's end skipped in groups of eight.  Tile scores
 // become order-preserving 32-bit keys (-0 folded into +0).  A per-lane
 // top-3 pre-filter bounds the R-th largest key from below (R = min(max(W -
 // |F|, m + 1), |C|): the listed candidates, and at least the m + 1 that
@@ -40,8 +41,9 @@
 // index) and ordered by (key, ~index) with a bitonic sort: in registers
 // across lanes for R <= 128, in LDS above.  sigma uses IEEE fp32 subtract and
 // divide.  The kernel is bound by instruction issue, not by its reads: on
-// the 128K layer about 1,620 VALU instructions per unit keep the SIMDs'
-// VALU issue ~84% busy.  Splitting the stages keeps each kernel at its own
+// the 128K layer 1,620 VALU instructions per unit kept the SIMDs' VALU
+// issue 84% busy (0.20 ms; skipped groups and the three-operand median in the
+// pre-filter took 5% off scores and selection at 1021 blocks, 0.291 -> 0.275).  Splitting the stages keeps each kernel at its own
 // occupancy (the scoring kernel is bound by registers, the selection
 // kernel by instruction issue).
 #include "select_common.h"
@@ -83,10 +85,9 @@ __device__ __forceinline__ float wave_max16(float x) {
 
 constexpr int kSurvivors = 256;   // pre-filter survivors handled in registers
 
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) x = min(x, (uint32_t)__shfl_xor((int)x, o));
-  return x;
+// Median of three keys (v_med3_u32, matched from this form).
+__device__ __forceinline__ uint32_t umed3(uint32_t a, uint32_t b, uint32_t x) {
+  return max(min(a, b), min(max(a, b), x));
 }
 
 // Workgroup barrier without a memory fence (the metadata ring's direct-to-LDS
@@ -493,53 +494,77 @@ __global__ void __launch_bounds__(64 * kSelWaves) select_kernel(SelParams P) {
   }
 
   // ---- the R largest keys, compacted into s_sel as (key, ~position) -------
+  // Slots are handled in groups of kGroup, each skipped as one by the waves
+  // whose row ends before it (a wave's rows are on average half of N_B long).
   // Pre-filter: each lane's three largest keys form a subset of the keys, so
   // the R-th largest of those 192 values, T0, is at most the R-th largest
   // key (R <= 192): the R largest are among {key >= T0}, typically R plus a
   // few dozen of up to 2046.  Those survivors, in position order, go
-  // through the exact selection; otherwise every candidate does.
+  // through the exact selection; otherwise every candidate does.  A row of at
+  // most 128 candidates goes to the register sort whole.
   constexpr int kMaxSlots = SLOTS;
+  constexpr int kGroup = SLOTS < 8 ? SLOTS : 8;
   const int nslots = (nc + 63) / 64;
   uint32_t keys[kMaxSlots];
-  {
-    // every load first (clamped in-row addresses), then the conversions, so
-    // the loads are in flight together
-    float raw[kMaxSlots];
 #pragma unroll
-    for (int sl = 0; sl < kMaxSlots; ++sl) {
-      const int p = 64 * sl + lane;
-      raw[sl] = (sl < nslots) ? src[p < nc ? p : nc - 1] : 0.f;
-    }
+  for (int s0 = 0; s0 < kMaxSlots; s0 += kGroup) {
+    if (s0 < nslots) {
+      // the group's loads first (clamped in-row addresses), then the
+      // conversions, so the loads are in flight together
+      float raw[kGroup];
 #pragma unroll
-    for (int sl = 0; sl < kMaxSlots; ++sl) {
-      const int p = 64 * sl + lane;
-      keys[sl] = (sl < nslots && p < nc) ? order_key(raw[sl]) : 0u;  // valid keys are >= 0x007fffff
+      for (int j = 0; j < kGroup; ++j) {
+        const int p = 64 * (s0 + j) + lane;
+        raw[j] = src[p < nc ? p : nc - 1];
+      }
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j)
+        keys[s0 + j] = (64 * (s0 + j) + lane < nc) ? order_key(raw[j]) : 0u;  // valid keys are >= 0x007fffff
+    } else {
+#pragma unroll
+      for (int j = 0; j < kGroup; ++j) keys[s0 + j] = 0u;
     }
   }
   bool filtered = false, sort_all = false;
-  if (R <= 192 && nc > R) {
-    // (slots past the row hold key 0, the smallest: no guard needed here or
-    // in the compaction below, where only keys >= t0 > 0 are taken)
+  const bool whole = nc <= 128 && R <= 128;
+  if (whole) {
+    sort_all = true;
+    filtered = true;
+  } else if (R <= 192 && nc > R) {
+    // (slots past the row hold key 0, the smallest: no guard needed within a
+    // group here or in the compaction below, where only keys >= t0 > 0 are
+    // taken)
     uint32_t top3[3] = {0u, 0u, 0u};
 #pragma unroll
-    for (int sl = 0; sl < kMaxSlots; ++sl) {
-      const uint32_t x = keys[sl];
-      top3[2] = max(top3[2], min(top3[1], x));
-      top3[1] = max(top3[1], min(top3[0], x));
-      top3[0] = max(top3[0], x);
+    for (int s0 = 0; s0 < kMaxSlots; s0 += kGroup) {
+      if (s0 < nslots) {
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+          const uint32_t x = keys[s0 + j];
+          top3[2] = umed3(top3[1], top3[2], x);
+          top3[1] = umed3(top3[0], top3[1], x);
+          top3[0] = max(top3[0], x);
+        }
+      }
     }
     bool exact0;
     const uint32_t t0 = kth_largest<3>(top3, 3, R, &exact0);
     if (t0 > 0u) {
       int ns = 0;
 #pragma unroll
-      for (int sl = 0; sl < kMaxSlots; ++sl) {
-        const bool take = keys[sl] >= t0;
-        const uint64_t mk = __ballot(take);
-        const int at = ns + lanes_below(mk);
-        if (take && at < kSurvivors)
-          s_sel[at] = ((uint64_t)keys[sl] << 32) | (uint32_t)(64 * sl + lane);
-        ns += __popcll(mk);
+      for (int s0 = 0; s0 < kMaxSlots; s0 += kGroup) {
+        if (s0 < nslots) {
+#pragma unroll
+          for (int j = 0; j < kGroup; ++j) {
+            const int sl = s0 + j;
+            const bool take = keys[sl] >= t0;
+            const uint64_t mk = __ballot(take);
+            const int at = ns + lanes_below(mk);
+            if (take && at < kSurvivors)
+              s_sel[at] = ((uint64_t)keys[sl] << 32) | (uint32_t)(64 * sl + lane);
+            ns += __popcll(mk);
+          }
+        }
       }
       if (ns <= 128 && R <= 128) {
         // few survivors: the register sort below orders all of them, and
@@ -586,8 +611,14 @@ __global__ void __launch_bounds__(64 * kSelWaves) select_kernel(SelParams P) {
     wave_lds_sync();
     const int n_in = sort_all ? 128 : R;   // entries to order (unused ones are 0)
     uint64_t e[2];
-    e[0] = (lane < n_in) ? s_sel[lane] : 0ull;
-    e[1] = (64 + lane < n_in) ? s_sel[64 + lane] : 0ull;
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl) {
+      const int i = 64 * sl + lane;
+      if (whole)
+        e[sl] = (sl < kMaxSlots && i < nc) ? ((uint64_t)keys[sl < kMaxSlots ? sl : 0] << 32) | (0xffffffffu - (uint32_t)i) : 0ull;
+      else
+        e[sl] = (i < n_in) ? s_sel[i] : 0ull;
+    }
 #pragma unroll
     for (int size = 2; size <= 128; size <<= 1) {
 #pragma unroll
@@ -693,6 +724,12 @@ hipError_t launch_select_s(const SelParams& P, hipStream_t stream) {
 template <bool PACKED>
 hipError_t launch_select(const SelParams& P, hipStream_t stream) {
   static_assert(UGBS_MAX_BLOCKS <= 64 * 64, "at most 64 slots per lane");
+  // The kernel for the shortest row that holds N_B: every wave runs through all
+  // of its slots' code (28/4 heads, 512 blocks: 97.4 -> 86.9 us for scores and
+  // selection with 8 slots for 32; 32/8 heads, 64 blocks: 21.2 -> 17.3 with 4).
+  if (P.s.NB <= 4 * 64) return launch_select_s<PACKED, 4>(P, stream);
+  if (P.s.NB <= 8 * 64) return launch_select_s<PACKED, 8>(P, stream);
+  if (P.s.NB <= 16 * 64) return launch_select_s<PACKED, 16>(P, stream);
   return P.s.NB <= 32 * 64 ? launch_select_s<PACKED, 32>(P, stream) : launch_select_s<PACKED, 64>(P, stream);
 }
 
