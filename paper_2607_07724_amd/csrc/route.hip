@@ -2,15 +2,11 @@
 // expansion (A.7-A.9; Eq. (trigger)).
 //
 // The quantile couples every tile of a sequence, so this is the pipeline's
-// one device-wide step.  It runs as two launches:
-//   route_stats : one 1024-thread workgroup per sequence.  sigma_bar[t] is
-//                 the fp32 sum over heads in head order, divided by H.  The
-//                 n_trig-th smallest sigma_bar of the population is found by
-//                 a most-significant-bit-first radix descent (sigma_bar >= 0,
-//                 so its bit pattern is order preserving); trigger[t] is
-//                 (t in P) and sigma_bar[t] <= tau.
-//   route_patch : one wave per kv_idx row; slots k..W-1 of tiles that do
-//                 not trigger become the sentinel N_B.
+// one device-wide step.  sigma_bar[t] is the fp32 sum over heads in head order,
+// divided by H; the n_trig-th smallest sigma_bar of the population is found by
+// a radix descent on its bit pattern (sigma_bar >= 0, so that is order
+// preserving); trigger[t] is (t in P) and sigma_bar[t] <= tau; slots k..W-1 of
+// the kv_idx rows of tiles that do not trigger become the sentinel N_B.
 // n_pop and n_trig = ceil(q n_pop) depend only on N, k and q and are
 // computed on the host, so no device-to-host synchronisation is needed.
 #include <mutex>
@@ -42,12 +38,76 @@ struct RouteParams {
   uint8_t* ws_trigger;
 };
 
-__global__ void __launch_bounds__(kStatsThreads) route_stats_kernel(RouteParams P) {
+// The n-th smallest (n >= 1) of `count` keys in LDS, by one wave: a
+// most-significant-bit-first radix descent over keys in registers, counting
+// with ballots, that ends once exactly n keys are at or below the candidate.
+__device__ __forceinline__ uint32_t nth_smallest(const uint32_t* keys, int count, int n, int lane) {
+  constexpr int kSlots = UGBS_MAX_BLOCKS / 64, kGroup = 8;
+  const int nslots = (count + 63) / 64;
+  uint32_t key[kSlots];
+#pragma unroll
+  for (int g = 0; g < kSlots; g += kGroup)
+    if (g < nslots) {
+#pragma unroll
+      for (int j = g; j < g + kGroup; ++j) key[j] = 64 * j + lane < count ? keys[64 * j + lane] : 0xffffffffu;
+    }
+  uint32_t ans = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = ans | ((1u << bit) - 1u);
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < kSlots; g += kGroup)
+      if (g < nslots) {
+#pragma unroll
+        for (int j = g; j < g + kGroup; ++j) cnt += (int)__popcll(__ballot(key[j] <= c));
+      }
+    if (cnt == n) {                       // the answer is the largest key <= c
+      uint32_t m = 0;
+#pragma unroll
+      for (int g = 0; g < kSlots; g += kGroup)
+        if (g < nslots) {
+#pragma unroll
+          for (int j = g; j < g + kGroup; ++j) m = max(m, key[j] <= c ? key[j] : 0u);
+        }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+      return m;
+    }
+    if (cnt < n) ans |= 1u << bit;
+  }
+  return ans;
+}
+
+template <int V>
+__device__ __forceinline__ void load_slots(const int32_t* p, int32_t (&v)[V]) {
+  if constexpr (V == 4) {
+    const int4 x = *reinterpret_cast<const int4*>(p);
+    v[0] = x.x, v[1] = x.y, v[2] = x.z, v[3] = x.w;
+  } else {
+    v[0] = *p;
+  }
+}
+template <int V>
+__device__ __forceinline__ void store_slots(int32_t* p, const int32_t (&v)[V]) {
+  if constexpr (V == 4)
+    *reinterpret_cast<int4*>(p) = make_int4(v[0], v[1], v[2], v[3]);
+  else
+    *p = v[0];
+}
+
+// One launch.  Every workgroup of a sequence (n_wg of them) computes the
+// sequence's sigma_bar, tau and flags for itself, out of the L2 and through no
+// more than two barriers; the first one stores them, and all of them share the
+// kv_idx rows to patch.  Two launches, statistics then patch with 32 barriered
+// radix steps, took 12.7 + 3.6 us at 16 tiles, 17.3 + 6.1 us at 512 tiles and 28
+// heads, 21.5 + 17.8 us at 2048 tiles and 32 heads. Launches back to back, two
+// launches / this one: 14.3 / 7.0, 18.0 / 12.7, 37.1 / 32.3, at 4096 tiles 57 / 50 us.
+template <int V>
+__global__ void __launch_bounds__(kStatsThreads) route_kernel(RouteParams P, int n_wg, int lg_row, int in_place) {
   __shared__ uint32_t s_key[UGBS_MAX_BLOCKS];
-  __shared__ int s_cnt[2][kStatsThreads / 64];
   __shared__ float s_tau;
   const Shape& s = P.s;
-  const int b = blockIdx.x;
+  const int b = blockIdx.x / n_wg, part = blockIdx.x - b * n_wg;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
 
   for (int t = tid; t < s.T; t += kStatsThreads) {
@@ -55,16 +115,16 @@ __global__ void __launch_bounds__(kStatsThreads) route_stats_kernel(RouteParams 
     uint32_t key = 0xffffffffu;
     if (in_population(t, s.k)) {
 #pragma clang fp contract(off)
-      // fp32 sum in head order; the loads of 8 heads are issued together
+      // fp32 sum in head order; the loads of 16 heads are issued together
       // before their adds (the order of the adds is unchanged)
       const float* col = P.sigma + (size_t)b * s.H * s.T + t;
       float acc = 0.0f;
-      for (int h0 = 0; h0 < s.H; h0 += 8) {
-        float v[8];
+      for (int h0 = 0; h0 < s.H; h0 += 16) {
+        float v[16];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = (h0 + j < s.H) ? col[(size_t)(h0 + j) * s.T] : 0.0f;
+        for (int j = 0; j < 16; ++j) v[j] = (h0 + j < s.H) ? col[(size_t)(h0 + j) * s.T] : 0.0f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < 16; ++j)
           if (h0 + j < s.H) acc += v[j];
       }
       sb = __fdiv_rn(acc, (float)s.H);
@@ -72,67 +132,72 @@ __global__ void __launch_bounds__(kStatsThreads) route_stats_kernel(RouteParams 
       key = __float_as_uint(sb);
     }
     s_key[t] = key;
-    P.ws_sigma_bar[(size_t)b * s.T + t] = sb;
-    if (P.sigma_bar) P.sigma_bar[(size_t)b * s.T + t] = sb;
-  }
-  __syncthreads();
-
-  float tau = -1.0f;
-  if (P.n_trig > 0) {
-    // smallest v with #{key <= v} >= n_trig
-    uint32_t ans = 0;
-    for (int bit = 31; bit >= 0; --bit) {
-      const uint32_t c = ans | ((1u << bit) - 1u);
-      int local = 0;
-      for (int t = tid; t < s.T; t += kStatsThreads) local += (s_key[t] <= c) ? 1 : 0;
-      // local is 0..4 for T <= 4096 (1024 threads); wave-reduce bit by bit
-      static_assert(UGBS_MAX_BLOCKS <= 7 * kStatsThreads, "per-thread count must fit in 3 bits");
-      const int wsum = __popcll(__ballot(local & 1)) + 2 * __popcll(__ballot(local & 2)) +
-                       4 * __popcll(__ballot(local & 4));
-      const int buf = bit & 1;
-      if (lane == 0) s_cnt[buf][wv] = wsum;
-      __syncthreads();
-      int cnt = 0;
-#pragma unroll
-      for (int w = 0; w < kStatsThreads / 64; ++w) cnt += s_cnt[buf][w];
-      if (cnt < P.n_trig) ans |= (1u << bit);
+    if (part == 0) {
+      P.ws_sigma_bar[(size_t)b * s.T + t] = sb;
+      if (P.sigma_bar) P.sigma_bar[(size_t)b * s.T + t] = sb;
     }
-    tau = __uint_as_float(ans);
   }
-  if (tid == 0) s_tau = tau;
   __syncthreads();
-  tau = s_tau;
-  if (tid == 0) {
-    P.ws_tau[b] = tau;
-    if (P.tau) P.tau[b] = tau;
+  if (wv == 0) {
+    const float tau = P.n_trig > 0 ? __uint_as_float(nth_smallest(s_key, s.T, P.n_trig, lane)) : -1.0f;
+    if (lane == 0) s_tau = tau;
   }
-  for (int t = tid; t < s.T; t += kStatsThreads) {
-    const uint8_t trig = (P.n_trig > 0 && s_key[t] != 0xffffffffu &&
-                          __uint_as_float(s_key[t]) <= tau) ? 1 : 0;
-    P.ws_trigger[(size_t)b * s.T + t] = trig;
-    if (P.trigger) P.trigger[(size_t)b * s.T + t] = trig;
+  __syncthreads();
+  const float tau = s_tau;
+  auto triggered = [&](int t) {
+    return P.n_trig > 0 && s_key[t] != 0xffffffffu && __uint_as_float(s_key[t]) <= tau;
+  };
+  if (part == 0) {
+    if (tid == 0) {
+      P.ws_tau[b] = tau;
+      if (P.tau) P.tau[b] = tau;
+    }
+    for (int t = tid; t < s.T; t += kStatsThreads) {
+      const uint8_t trig = triggered(t) ? 1 : 0;
+      P.ws_trigger[(size_t)b * s.T + t] = trig;
+      if (P.trigger) P.trigger[(size_t)b * s.T + t] = trig;
+    }
   }
-}
+  if (!P.kv_idx) return;
 
-// One wave per kv_idx row (b, h, t), rows grid-strided.  In place only the
-// slots k..W-1 of rows whose tile does not trigger are written.
-__global__ void __launch_bounds__(256) route_patch_kernel(RouteParams P, long n_rows,
-                                                          int in_place) {
-  const Shape& s = P.s;
-  const int lane = threadIdx.x & 63;
-  const long wave0 = (long)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-  const long n_waves = (long)gridDim.x * (blockDim.x / 64);
-  for (long row = wave0; row < n_rows; row += n_waves) {
-    const int t = (int)(row % s.T);
-    const int b = (int)(row / ((long)s.T * s.H));
-    const bool trig = P.ws_trigger[(size_t)b * s.T + t] != 0;
-    int32_t* dst = P.kv_idx + row * s.W;
-    if (in_place) {
-      if (trig) continue;
-      for (int slot = s.k + lane; slot < s.W; slot += 64) dst[slot] = s.NB;
-    } else {
-      const int32_t* src = P.idx_sorted + row * s.W;
-      for (int slot = lane; slot < s.W; slot += 64) dst[slot] = (slot < s.k || trig) ? src[slot] : s.NB;
+  // Slots k..W-1 of the rows whose tile does not trigger become the sentinel
+  // N_B.  V slots a lane (16-byte accesses), 2^lg_row lanes a row (short rows
+  // share a wave), and kBatch rows of every lane in flight together: the copy
+  // is bound by the bytes in flight, one workgroup per CU.
+  const int per = 64 >> lg_row, sub = lane >> lg_row, first = (lane & ((1 << lg_row) - 1)) * V;
+  const int n_rows = s.H * s.T;
+  const int step = n_wg * (kStatsThreads / 64) * per;
+  const size_t base = (size_t)b * n_rows * s.W;
+  constexpr int kBatch = 4;
+  for (int r0 = (part * (kStatsThreads / 64) + wv) * per + sub; r0 < n_rows; r0 += kBatch * step) {
+    for (int slot = first; slot < s.W; slot += V << lg_row) {
+      int32_t v[kBatch][V];
+      bool trig[kBatch];
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int r = r0 + i * step;
+        if (r >= n_rows) break;
+        trig[i] = triggered(r % s.T);
+        if (in_place || (slot >= s.k && !trig[i])) continue;
+        load_slots<V>(P.idx_sorted + base + (size_t)r * s.W + slot, v[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < kBatch; ++i) {
+        const int r = r0 + i * step;
+        if (r >= n_rows) break;
+        int32_t* dst = P.kv_idx + base + (size_t)r * s.W + slot;
+        if (in_place) {
+          if (trig[i] || slot + V <= s.k) continue;
+#pragma unroll
+          for (int e = 0; e < V; ++e)
+            if (slot + e >= s.k) dst[e] = s.NB;
+        } else {
+#pragma unroll
+          for (int e = 0; e < V; ++e)
+            if (slot + e >= s.k && !trig[i]) v[i][e] = s.NB;
+          store_slots<V>(dst, v[i]);
+        }
+      }
     }
   }
 }
@@ -185,14 +250,21 @@ hipError_t launch_route(const Shape& s, int n_pop, int n_trig, const float* sigm
   P.ws_sigma_bar = reinterpret_cast<float*>(ws + ws_sigma_bar_off(s));
   P.ws_tau = reinterpret_cast<float*>(ws + ws_tau_off(s));
   P.ws_trigger = ws + ws_trigger_off(s);
-  route_stats_kernel<<<s.B, kStatsThreads, 0, stream>>>(P);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !kv_idx) return e;  // no lists to patch: flags only
-  const long n_rows = (long)s.B * s.H * s.T;
-  long blocks = (n_rows + 3) / 4;
-  if (blocks > 65536) blocks = 65536;
-  route_patch_kernel<<<(unsigned)blocks, 256, 0, stream>>>(P, n_rows,
-                                                           idx_sorted == kv_idx ? 1 : 0);
+  // four slots a lane where rows and pointers are 16-byte aligned
+  const bool quad = s.W % 4 == 0 && ((reinterpret_cast<uintptr_t>(idx_sorted) | reinterpret_cast<uintptr_t>(kv_idx)) & 15) == 0;
+  const int lanes = quad ? s.W / 4 : s.W;
+  int lg_row = 0;
+  while (lg_row < 6 && (1 << lg_row) < lanes) ++lg_row;
+  // at least four rows per lane, and no more workgroups than CUs
+  const long per_wg = 4l * (kStatsThreads >> lg_row);
+  const long rounds = kv_idx ? ((long)s.H * s.T + per_wg - 1) / per_wg : 1;
+  const long most = s.B < 256 ? 256 / s.B : 1;
+  const int n_wg = (int)(rounds < most ? rounds : most);
+  const int in_place = idx_sorted == kv_idx ? 1 : 0;
+  if (quad)
+    route_kernel<4><<<(unsigned)(s.B * n_wg), kStatsThreads, 0, stream>>>(P, n_wg, lg_row, in_place);
+  else
+    route_kernel<1><<<(unsigned)(s.B * n_wg), kStatsThreads, 0, stream>>>(P, n_wg, lg_row, in_place);
   return hipGetLastError();
 }
 
