@@ -1,9 +1,9 @@
 // Stages 2+3: tile scores, forcing, sorted top-2k and the cutoff margin
 // (A.2-A.6; Eqs. (tile-score), (sigma-def)).  Two kernels on one stream.
 //
-// score_kernel: one workgroup per 4 consecutive (Q-tile, query head) units
-// of one (batch, kv head), sibling heads of one tile or of two adjacent
-// tiles (see Group); each wave owns one unit (64 rows of its tile).
+// score_kernel: one workgroup per 4 (or 8) consecutive (Q-tile, query head)
+// units of one (batch, kv head), sibling heads of one tile or of adjacent
+// tiles (see Group); each wave owns one unit (64 rows of its tile), or two.
 // Scoring is a contraction on the matrix cores:
 //   S[64 rows x 16 blocks] = Q[64 x d] * M[d x 16 blocks]
 // K-mean: M = kbar, dense bf16 MFMA (v_mfma_f32_16x16x32_bf16).  Quest: the
@@ -51,7 +51,7 @@
 namespace ugbs {
 namespace {
 
-constexpr int kMaxGroup = 4;    // sibling query heads per workgroup
+constexpr int kMaxGroup = 4;    // waves per score workgroup
 constexpr int kSelWaves = 4;    // units (waves) per selection workgroup
 
 #define LDS_AS __attribute__((address_space(3)))
@@ -66,7 +66,8 @@ struct SelParams {
   float* sigma;
   float* scratch; // packed candidate scores (workspace), when neither scores_in nor scores_out
   double* rough;  // per-unit row roughness (diagnostics mode of the score kernel)
-  int GW;         // waves (query heads) per workgroup of the score kernel
+  int GW;         // waves per workgroup of the score kernel
+  int per;        // units per workgroup of the score kernel
   int n_groups;   // score workgroups per (b, kv head) = ceil(T G / GW)
   int n_wg;       // score-kernel workgroups
   int wave_lds;   // bytes of per-wave LDS of the selection kernel (survivors)
@@ -149,18 +150,18 @@ struct MetaChunk {
 
 // Workgroup ordering (ids dealt round-robin to the XCDs, see Unit): (b, kv
 // head) outermost; within it the units (tile, query head) in the order
-// heaviest tile first, sibling heads adjacent, taken GW at a time.  With G
-// a multiple of GW a workgroup holds sibling heads of one tile; otherwise
-// (G = 7: 4 + 3) a workgroup may hold the last heads of tile t and the
-// first of tile t - 1, whose candidate ranges differ by one block, so the
-// metadata chunks are still shared and no wave idles.
+// heaviest tile first, sibling heads adjacent, taken `per` at a time.  With G
+// a multiple of it a workgroup holds sibling heads of one tile; otherwise a
+// workgroup spans tiles (G = 7: the last heads of tile t and the first of tile
+// t - 1; G = 1: four tiles), whose candidate ranges differ by a block each, so
+// the metadata chunks are still shared and no wave idles.
 struct Group {
   int b, kvh, u0;   // u0: the first unit (tile rank * G + head) of the workgroup
 };
 
 __device__ __forceinline__ Group group_of(int id, const SelParams& P) {
   Group r;
-  r.u0 = (id % P.n_groups) * P.GW;
+  r.u0 = (id % P.n_groups) * P.per;
   const int rest = id / P.n_groups;
   r.kvh = rest % P.s.Hkv;
   r.b = rest / P.s.Hkv;
@@ -199,7 +200,7 @@ __device__ __forceinline__ float row_diff_sq(const f32x4 (&acc)[4], int lane) {
   return sq;
 }
 
-template <int D, bool QUEST, int OUT>
+template <int D, bool QUEST, int OUT, int NU = 1>
 __device__ __forceinline__ void score_body(const SelParams& P) {
   constexpr bool PACKED = OUT == kOutPacked;
   constexpr bool ROUGH = OUT == kOutRough;
@@ -215,13 +216,20 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
   const int id = blockIdx.x;
   if (id >= P.n_wg) return;
   const Group gr = group_of(id, P);
-  const int x = gr.u0 + w;                            // this wave's unit within the (b, kv head)
-  const bool active = x < s.T * s.G;                  // the last workgroup may be partial
-  const int xs = active ? x : gr.u0;
-  const int h = gr.kvh * s.G + xs % s.G;
-  const int t = s.T - 1 - xs / s.G;
-  const size_t row = ((size_t)gr.b * s.H + h) * s.T + t;
-  const int nc = (t >= 1) ? t - 1 : 0;
+  // this wave's NU units within the (b, kv head); the last workgroup may be partial
+  bool active[NU];
+  int h[NU], t[NU], nc[NU];
+  size_t row[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    const int x = gr.u0 + w * NU + u;
+    active[u] = x < s.T * s.G;
+    const int xs = active[u] ? x : gr.u0;
+    h[u] = gr.kvh * s.G + xs % s.G;
+    t[u] = s.T - 1 - xs / s.G;
+    row[u] = ((size_t)gr.b * s.H + h[u]) * s.T + t[u];
+    nc[u] = (t[u] >= 1) ? t[u] - 1 : 0;
+  }
   // the workgroup's heaviest tile (wave 0's) sets the candidate range the
   // metadata chunks cover; waves of the next tile use one block less
   const int t_top = s.T - 1 - gr.u0 / s.G;
@@ -230,20 +238,25 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
   unsigned char* ring = smem;
 
   // this unit's candidate scores 1..nc: packed rows, or the full [.., N_B] row
-  float* dst = PACKED ? P.scratch + packed_row(gr.b * s.H + h, t, s.T)
-                      : (ROUGH ? nullptr : P.scores_out + row * s.NB + 1);
+  float* dst[NU];
+#pragma unroll
+  for (int u = 0; u < NU; ++u)
+    dst[u] = PACKED ? P.scratch + packed_row(gr.b * s.H + h[u], t[u], s.T)
+                    : (ROUGH ? nullptr : P.scores_out + row[u] * s.NB + 1);
   double rough = 0.0;
   if (nc_top > 0) {
     // ---- A operand: this wave's 64 query rows, raw, for both backbones;
     // Quest adds the 2:4 sparsity indices that select kmax or kmin per
     // channel by the sign of q (see quest_index)
     constexpr int KA = D / 32;
-    bf16x8 a[4][KA];
-    uint32_t qidx[4][QUEST ? KA : 1];
-    const uint16_t* qtile = P.Q + (((size_t)gr.b * s.H + h) * s.N + (size_t)t * kBlock) * D;
+    constexpr int RT = 4 * NU;                  // 16-row tiles, unit by unit
+    bf16x8 a[RT][KA];
+    uint32_t qidx[RT][QUEST ? KA : 1];
 #pragma unroll
-    for (int rt = 0; rt < 4; ++rt) {
-      const uint16_t* qrow = qtile + (size_t)(16 * rt + c16) * D;
+    for (int rt = 0; rt < RT; ++rt) {
+      const int u = rt / 4;
+      const uint16_t* qtile = P.Q + (((size_t)gr.b * s.H + h[u]) * s.N + (size_t)t[u] * kBlock) * D;
+      const uint16_t* qrow = qtile + (size_t)(16 * (rt % 4) + c16) * D;
 #pragma unroll
       for (int ks = 0; ks < KA; ++ks) {
         const uint4 v = *reinterpret_cast<const uint4*>(qrow + 32 * ks + 8 * g);
@@ -310,7 +323,7 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's reads of chunk c-1 are done
       lds_barrier();                                    // chunk c landed; chunk c-1 is free
       if (c + MC::kRingSlots - 1 < nchunks) issue(c + MC::kRingSlots - 1);
-      if (active) {
+      if (active[0]) {
         const unsigned char* slot = ring + (c % MC::kRingSlots) * MC::kBytes;
         constexpr int NCT = MC::kBlocks / 16;            // 16-block column tiles per chunk
         // Read-ahead form (Quest d <= 128, K-mean d 256; elsewhere the
@@ -334,6 +347,7 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
         // the roughness mode keeps its registers for the row differences and
         // reads each column tile's operands at the tile's start
         constexpr bool EARLY = AHEAD && !ROUGH;
+        __builtin_amdgcn_s_setprio(1);   // matrix work ahead of other waves' max and stores (0.5-1%)
         if constexpr (AHEAD) {
           read_b(0);
           __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the matrix instructions
@@ -345,21 +359,21 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
             if (ct > 0) read_b(ct);
             __builtin_amdgcn_sched_barrier(0);
           }
-          f32x4 acc[4];
+          f32x4 acc[RT];
 #pragma unroll
-          for (int rt = 0; rt < 4; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
           if constexpr (AHEAD) {
 #pragma unroll
             for (int ks = 0; ks < KS / (QUEST ? 2 : 1); ++ks) {
               if constexpr (QUEST) {
                 const bf16x16 b = as_bf16x16(bb[2 * ks], bb[2 * ks + 1]);
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt)
+                for (int rt = 0; rt < RT; ++rt)
                   acc[rt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a[rt][ks], b, acc[rt], (int)qidx[rt][ks], 0, 0);
               } else {
                 const bf16x8 b = as_bf16x8(bb[ks]);
 #pragma unroll
-                for (int rt = 0; rt < 4; ++rt)
+                for (int rt = 0; rt < RT; ++rt)
                   acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt][ks], b, acc[rt], 0, 0, 0);
               }
             }
@@ -376,7 +390,7 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
               const uint4 b1 = *reinterpret_cast<const uint4*>(slot + MC::off(br, 8 * ks + 4 + g));
               const bf16x16 b = as_bf16x16(b0, b1);
 #pragma unroll
-              for (int rt = 0; rt < 4; ++rt)
+              for (int rt = 0; rt < RT; ++rt)
                 acc[rt] = __builtin_amdgcn_smfmac_f32_16x16x64_bf16(a[rt][ks], b, acc[rt], (int)qidx[rt][ks], 0, 0);
             }
           } else {
@@ -384,44 +398,53 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
             for (int ks = 0; ks < KS; ++ks) {
               const bf16x8 b = as_bf16x8(*reinterpret_cast<const uint4*>(slot + MC::off(br, 4 * ks + g)));
 #pragma unroll
-              for (int rt = 0; rt < 4; ++rt)
+              for (int rt = 0; rt < RT; ++rt)
                 acc[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rt][ks], b, acc[rt], 0, 0, 0);
             }
           }
+          __builtin_amdgcn_s_setprio(0);
           const int pos = MC::kBlocks * c + br;
           if constexpr (ROUGH) {
             const float sq = row_diff_sq(acc, lane);
-            rough += (pos < nc) ? (double)sq : 0.0;
+            rough += (pos < nc[0]) ? (double)sq : 0.0;
           } else {
-            float mx = acc[0][0];
-#pragma unroll
-            for (int rt = 0; rt < 4; ++rt)
-#pragma unroll
-              for (int i = 0; i < 4; ++i) mx = fmaxf(mx, acc[rt][i]);
-            mx = wave_max16(mx);
             // straight to memory: a 64-byte store per column tile.  The loop's vmcnt
             // waits still count ring loads correctly: loads complete in issue
             // order, so while a chunk is pending every later ring load is too,
             // and an earlier store in flight can only lengthen a wait
-            if (g == 0 && pos < nc) dst[pos] = mx;
+#pragma unroll
+            for (int u = 0; u < NU; ++u) {
+              float mx = acc[4 * u][0];
+#pragma unroll
+              for (int rt = 4 * u; rt < 4 * u + 4; ++rt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) mx = fmaxf(mx, acc[rt][i]);
+              mx = wave_max16(mx);
+              if (g == 0 && active[u] && pos < nc[u]) dst[u][pos] = mx;
+            }
           }
         }
       }
     }
   }
   if constexpr (ROUGH) {
-    if (active) {
+    static_assert(NU == 1, "one unit per wave");
+    if (active[0]) {
 #pragma unroll
       for (int o = 32; o >= 1; o >>= 1) rough += __shfl_xor(rough, o);
-      if (lane == 0) P.rough[row] = rough;
+      if (lane == 0) P.rough[row[0]] = rough;
     }
     return;
   }
-  if (!active || PACKED) return;
+  if (PACKED) return;
   // full layout: -inf outside C(t) = {1..t-1}
-  float* full = P.scores_out + row * s.NB;
-  for (int p = lane; p < s.NB; p += 64)
-    if (p == 0 || p > nc) full[p] = -__builtin_huge_valf();
+#pragma unroll
+  for (int u = 0; u < NU; ++u) {
+    if (!active[u]) continue;
+    float* full = P.scores_out + row[u] * s.NB;
+    for (int p = lane; p < s.NB; p += 64)
+      if (p == 0 || p > nc[u]) full[p] = -__builtin_huge_valf();
+  }
 }
 
 template <int D, bool QUEST, int OUT>
@@ -435,6 +458,16 @@ __global__ void __launch_bounds__(64 * kMaxGroup) score_kernel(SelParams P) {
 // one column tile's operands fit without spilling.  Measured at 128K:
 // score + select 1.50 -> 1.36 ms (P7 1.28 -> 1.18, C3 0.45 -> 0.41),
 // outputs bit-identical.
+// The same with two units per wave (249 registers, two waves per SIMD): each
+// metadata operand read from the LDS, and each chunk fetched into it, serves
+// twice the matrix instructions; the LDS reads and the staging were as long as
+// the matrix work (texture unit 51% busy, matrix cores 50%).
+template <int OUT>
+__global__ void __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(2, 2)))
+score_kernel_q128x2(SelParams P) {
+  score_body<128, true, OUT, 2>(P);
+}
+
 template <int OUT>
 __global__ void __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(3, 3)))
 score_kernel_q128(SelParams P) {
@@ -684,6 +717,13 @@ __global__ void __launch_bounds__(64 * kSelWaves) select_kernel(SelParams P) {
   }
 }
 
+// Score workgroups of `per` consecutive units of a (b, kv head).
+void set_groups(SelParams* P, int per) {
+  P->per = per;
+  P->n_groups = (P->s.T * P->s.G + per - 1) / per;
+  P->n_wg = P->s.B * P->s.Hkv * P->n_groups;
+}
+
 template <int D, bool QUEST, int OUT>
 hipError_t launch_score(SelParams P, hipStream_t stream) {
   using MC = MetaChunk<D, QUEST>;
@@ -697,7 +737,16 @@ hipError_t launch_score(SelParams P, hipStream_t stream) {
   const int grid = ((P.n_wg + 7) / 8) * 8;
   if constexpr (D == 128 && QUEST && OUT != kOutRough) {
     static_assert(MetaChunk<D, QUEST>::kRingSlots * MetaChunk<D, QUEST>::kBytes <= 65536, "static LDS limit");
-    score_kernel_q128<OUT><<<grid, 64 * P.GW, smem, stream>>>(P);
+    // Two units per wave where the rows are long and fill the chip for a few
+    // rounds (scores and selection, one / two units per wave: 32/8 heads at 128K
+    // 1.30 / 1.23 ms, 28/4 at 64K 354 / 338 us, 8/2 at 128K 332 / 316 us, but
+    // 28/4 at 32K 106.1 / 109.5 us, 32/8 at 16K 53.1 / 58.5 us).
+    if (P.s.T >= 1024 && P.s.B * P.s.H * P.s.T >= 16384) {
+      set_groups(&P, 2 * P.GW);
+      score_kernel_q128x2<OUT><<<((P.n_wg + 7) / 8) * 8, 64 * P.GW, smem, stream>>>(P);
+    } else {
+      score_kernel_q128<OUT><<<grid, 64 * P.GW, smem, stream>>>(P);
+    }
   } else if constexpr (D == 128 && !QUEST && OUT != kOutRough) {
     score_kernel_k128<OUT><<<grid, 64 * P.GW, smem, stream>>>(P);
   } else {
@@ -751,9 +800,12 @@ SelParams score_params(const Shape& s, const uint16_t* Q, const uint16_t* meta) 
   P.s = s;
   P.Q = Q;
   P.meta = meta;
-  P.GW = s.G < kMaxGroup ? s.G : kMaxGroup;
-  P.n_groups = (s.T * s.G + P.GW - 1) / P.GW;   // workgroups per (b, kv head)
-  P.n_wg = s.B * s.Hkv * P.n_groups;
+  // Four waves whatever the ratio of heads: with fewer than four query heads per
+  // kv head a workgroup takes units of adjacent tiles, which share all but a few
+  // of their candidates (6/3 heads at 32K, Quest: scores and selection 61 -> 41
+  // us against a workgroup per tile; 3/3 heads, d 64 at 64K 77 -> 50 us).
+  P.GW = kMaxGroup;
+  set_groups(&P, P.GW);
   return P;
 }
 
