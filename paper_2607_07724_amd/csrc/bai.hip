@@ -32,7 +32,7 @@ namespace {
 
 constexpr int kBaiUnits = 4;   // query heads of one tile per workgroup (one wave each)
 constexpr int kBaiSlots = UGBS_MAX_BLOCKS_ROWS / 64;
-constexpr int kHeadThreads = 256;
+constexpr int kHeadThreads = 512;
 
 struct TileParams {
   Shape s;
@@ -309,9 +309,9 @@ __device__ __forceinline__ long long block_sum_i(long long x, long long* red) {
 
 __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
 #pragma clang fp contract(off)
-  __shared__ float s_sig[UGBS_MAX_BLOCKS_ROWS], s_g[UGBS_MAX_BLOCKS_ROWS], s_r[UGBS_MAX_BLOCKS_ROWS],
+  __shared__ __align__(16) float s_sig[UGBS_MAX_BLOCKS_ROWS], s_g[UGBS_MAX_BLOCKS_ROWS], s_r[UGBS_MAX_BLOCKS_ROWS],
       s_d2[UGBS_MAX_BLOCKS_ROWS];
-  __shared__ int s_dk[UGBS_MAX_BLOCKS_ROWS];
+  __shared__ __align__(16) int s_dk[UGBS_MAX_BLOCKS_ROWS];
   __shared__ int s_n;
   __shared__ double s_red[kHeadThreads / 64];
   __shared__ long long s_redi[kHeadThreads / 64];
@@ -325,23 +325,31 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
   const ugbs_bai_tile* tl = P.tiles + (size_t)bh * s.T;
   const double q = s.q;
 
-  // ---- compact the valid tiles in tile order (wave 0) ---------------------
-  if (tid < 64) {
+  // ---- compact the valid tiles in tile order, kHeadThreads records at a time ----
+  {
+    const int lane = tid & 63, w = tid >> 6;
     int base = 0;
-    for (int t0 = 0; t0 < s.T; t0 += 64) {
+    for (int t0 = 0; t0 < s.T; t0 += kHeadThreads) {
       const int t = t0 + tid;
       ugbs_bai_tile x;
       const bool v = t < s.T && (x = tl[t], x.valid != 0);
       const uint64_t mk = __ballot(v);
+      if (lane == 0) s_redi[w] = (long long)__popcll(mk);
+      __syncthreads();
+      int i = base + lanes_below(mk);
+      for (int u = 0; u < kHeadThreads / 64; ++u) {
+        const int c = (int)s_redi[u];
+        i += u < w ? c : 0;
+        base += c;
+      }
       if (v) {
-        const int i = base + lanes_below(mk);
         s_sig[i] = x.sigma;
         s_g[i] = x.g;
         s_r[i] = x.r;
         s_d2[i] = x.delta2;
         s_dk[i] = x.fail_k - x.fail_rk;
       }
-      base += __popcll(mk);
+      __syncthreads();
     }
     if (tid == 0) s_n = base;
   }
@@ -364,16 +372,25 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
   const int i50 = (int)floor(0.5 * (double)(n - 1));
 
   // ---- mean and CV of r: left-to-right fp64 sums in tile order ------------
-  if (tid == 0) {
-    double sum = 0.0;
-    for (int i = 0; i < n; ++i) sum += (double)s_r[i];
-    const double mean = sum / n;
-    double var = 0.0;
-    for (int i = 0; i < n; ++i) {
-      const double dx = (double)s_r[i] - mean;
-      var += dx * dx;
-    }
-    var = var / n;
+  // One thread of the last wave, whose tiles come last in the rank counting
+  // below; 16 values are read ahead of their dependent adds (one LDS round trip
+  // per add took 30 us of the kernel's 66 at 448 tiles).
+  if (tid == kHeadThreads - 1) {
+    auto in_order = [&](auto&& term) {
+      double sum = 0.0;
+      int i = 0;
+      for (; i + 16 <= n; i += 16) {
+        float v[16];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) v[j] = s_r[i + j];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) sum += term((double)v[j]);
+      }
+      for (; i < n; ++i) sum += term((double)s_r[i]);
+      return sum;
+    };
+    const double mean = in_order([](double r) { return r; }) / n;
+    const double var = in_order([&](double r) { return (r - mean) * (r - mean); }) / n;
     s_rmean = mean;
     s_rcv = (mean != 0.0) ? __dsqrt_rn(var) / mean : nan;
   }
@@ -388,12 +405,21 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
     const float di = s_d2[i], si = s_sig[i];
     const int ki = s_dk[i];
     int rd = 0, rs = 0, rk = 0;
-    for (int j = 0; j < n; ++j) {
-      const float dj = s_d2[j], sj = s_sig[j];
-      const int kj = s_dk[j];
-      rd += (dj < di) || (dj == di && j < i);
-      rs += (sj < si) || (sj == si && j < i);
-      rk += (kj > ki) || (kj == ki && j < i);
+    // four tiles a step (the entries past n are read but not counted)
+    for (int j0 = 0; j0 < n; j0 += 4) {
+      const float4 d4 = *reinterpret_cast<const float4*>(s_d2 + j0);
+      const float4 s4 = *reinterpret_cast<const float4*>(s_sig + j0);
+      const int4 k4 = *reinterpret_cast<const int4*>(s_dk + j0);
+      const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
+      const int kv[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = j0 + e;
+        const bool in = j < n, before = j < i;
+        rd += in && ((dv[e] < di) || (dv[e] == di && before));
+        rs += in && ((sv[e] < si) || (sv[e] == si && before));
+        rk += in && ((kv[e] > ki) || (kv[e] == ki && before));
+      }
     }
     if (rd == i05) s_pick[0] = di;
     if (rd == i50) s_pick[1] = di;
