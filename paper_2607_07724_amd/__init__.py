@@ -140,19 +140,41 @@ def ugbs_workspace_bytes(p: Problem) -> int:
 
 
 # ---------------------------------------------------------------- marshalling
+# A layer is four calls whose kernels take 40 us at 1K tokens, less than the
+# checks of their arguments took: torch is imported once, the stream is asked
+# for as a raw handle, and a call's sizes are read from the problem once.
+
+_torch = None
+_BF16 = ()
+_raw_stream = None
+
+
+def _load_torch():
+    global _torch, _BF16, _raw_stream
+    import torch
+    _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
+    _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _torch = torch
+    return torch
+
+
+def _get_torch():
+    return _torch or _load_torch()
+
 
 def _stream(stream):
     if stream is not None:
-        return ctypes.c_void_p(int(stream))
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return int(stream)
+    torch = _get_torch()
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(name, t, shape, dtypes, device=None):
-    import torch
     if t is None:
         raise ValueError(f"{name} is required")
-    if tuple(t.shape) != tuple(shape):
+    if t.shape != shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)} != expected {tuple(shape)}")
     if t.dtype not in dtypes:
         raise ValueError(f"{name}: dtype {t.dtype} not in {dtypes}")
@@ -162,7 +184,7 @@ def _check(name, t, shape, dtypes, device=None):
         raise ValueError(f"{name} is on {t.device}, expected {device}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _opt(name, t, shape, dtypes, device):
@@ -170,8 +192,7 @@ def _opt(name, t, shape, dtypes, device):
 
 
 def _bf16():
-    import torch
-    return (torch.bfloat16, torch.int16, torch.uint16)
+    return _BF16 or (_load_torch() and _BF16)
 
 
 def _raise(fn, st):
@@ -184,8 +205,9 @@ def ugbs_block_meta(p: Problem, K, meta, stream=None):
     (Quest: per channel the pair (min, max))."""
     bf = _bf16()
     dev = K.device
-    k = _check("K", K, (p.batch, p.n_kv_heads, p.seq_len, p.head_dim), bf)
-    m = _check("meta", meta, (p.batch, p.n_kv_heads, p.NB, p.head_dim, p.meta_width), bf, dev)
+    B, Hkv, N, d = p.batch, p.n_kv_heads, p.seq_len, p.head_dim
+    k = _check("K", K, (B, Hkv, N, d), bf)
+    m = _check("meta", meta, (B, Hkv, N // BLOCK, d, p.meta_width), bf, dev)
     _raise("ugbs_block_meta", lib().ugbs_block_meta(ctypes.byref(p), k, m, _stream(stream)))
 
 
@@ -194,18 +216,20 @@ def ugbs_score_select(p: Problem, Q, meta, idx_sorted, sigma, scores_in=None, sc
     """Stages 2-3 (A.2-A.6): -> idx_sorted [B,H,T,2k] int32 (or None: sigma
     only), sigma [B,H,T] fp32.  Without scores_in/scores_out the tile scores
     pass through `workspace` (>= ugbs_workspace_bytes(p) bytes)."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
-    q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
-    m = _check("meta", meta, (p.batch, p.n_kv_heads, p.NB, p.head_dim, p.meta_width), bf, dev)
-    si = _opt("scores_in", scores_in, (p.batch, p.n_heads, p.T, p.NB), (torch.float32,), dev)
-    so = _opt("scores_out", scores_out, (p.batch, p.n_heads, p.T, p.NB), (torch.float32,), dev)
-    ix = _opt("idx_sorted", idx_sorted, (p.batch, p.n_heads, p.T, p.W), (torch.int32,), dev)
-    sg = _check("sigma", sigma, (p.batch, p.n_heads, p.T), (torch.float32,), dev)
+    B, H, Hkv, N, d = p.batch, p.n_heads, p.n_kv_heads, p.seq_len, p.head_dim
+    T, f32 = N // BLOCK, (torch.float32,)
+    q = _check("Q", Q, (B, H, N, d), bf)
+    m = _check("meta", meta, (B, Hkv, T, d, p.meta_width), bf, dev)
+    si = _opt("scores_in", scores_in, (B, H, T, T), f32, dev)
+    so = _opt("scores_out", scores_out, (B, H, T, T), f32, dev)
+    ix = _opt("idx_sorted", idx_sorted, (B, H, T, p.W), (torch.int32,), dev)
+    sg = _check("sigma", sigma, (B, H, T), f32, dev)
     ws, nbytes = None, 0
     if workspace is not None:
-        ws = _check("workspace", workspace, tuple(workspace.shape), (workspace.dtype,), dev)
+        ws = _check("workspace", workspace, workspace.shape, (workspace.dtype,), dev)
         nbytes = workspace.numel() * workspace.element_size()
     _raise("ugbs_score_select",
            lib().ugbs_score_select(ctypes.byref(p), q, m, si, so, ix, sg, ws, nbytes, _stream(stream)))
@@ -214,7 +238,7 @@ def ugbs_score_select(p: Problem, Q, meta, idx_sorted, sigma, scores_in=None, sc
 def ugbs_quest_scores_valu(p: Problem, Q, meta, scores_out, stream=None):
     """Quest tile scores on the vector ALU (the literal per-channel form of
     Eq. (quest-score)): scores_out [B,H,T,N_B] fp32, -inf outside C(t)."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
     q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
@@ -228,23 +252,26 @@ def ugbs_route(p: Problem, sigma, idx_sorted, kv_idx, workspace, sigma_bar=None,
                trigger=None, stream=None):
     """Stage 4 (A.7-A.9): sigma, idx_sorted -> kv_idx (may be idx_sorted itself);
     idx_sorted and kv_idx both None: statistics and trigger flags only."""
-    import torch
+    torch = _get_torch()
     dev = sigma.device
-    sg = _check("sigma", sigma, (p.batch, p.n_heads, p.T), (torch.float32,))
+    B, H, T, W = p.batch, p.n_heads, p.T, p.W
+    f32 = (torch.float32,)
+    sg = _check("sigma", sigma, (B, H, T), f32)
     if (idx_sorted is None) != (kv_idx is None):
         raise ValueError("idx_sorted and kv_idx are given together or not at all")
-    ix = _opt("idx_sorted", idx_sorted, (p.batch, p.n_heads, p.T, p.W), (torch.int32,), dev)
-    kv = _opt("kv_idx", kv_idx, (p.batch, p.n_heads, p.T, p.W), (torch.int32,), dev)
-    need = ugbs_workspace_bytes(p)
-    if workspace is None or workspace.numel() * workspace.element_size() < need:
-        raise ValueError(f"workspace must hold >= {need} bytes")
-    ws = _check("workspace", workspace, tuple(workspace.shape), (workspace.dtype,), dev)
-    sb = _opt("sigma_bar", sigma_bar, (p.batch, p.T), (torch.float32,), dev)
-    ta = _opt("tau", tau, (p.batch,), (torch.float32,), dev)
-    tr = _opt("trigger", trigger, (p.batch, p.T), (torch.uint8,), dev)
-    _raise("ugbs_route", lib().ugbs_route(ctypes.byref(p), sg, ix, kv, sb, ta, tr, ws,
-                                          workspace.numel() * workspace.element_size(),
-                                          _stream(stream)))
+    ix = _opt("idx_sorted", idx_sorted, (B, H, T, W), (torch.int32,), dev)
+    kv = _opt("kv_idx", kv_idx, (B, H, T, W), (torch.int32,), dev)
+    nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    if workspace is None or (nbytes == 0 and ugbs_workspace_bytes(p) > 0):
+        raise ValueError(f"workspace must hold >= {ugbs_workspace_bytes(p)} bytes")
+    ws = _check("workspace", workspace, workspace.shape, (workspace.dtype,), dev)
+    sb = _opt("sigma_bar", sigma_bar, (B, T), f32, dev)
+    ta = _opt("tau", tau, (B,), f32, dev)
+    tr = _opt("trigger", trigger, (B, T), (torch.uint8,), dev)
+    st = lib().ugbs_route(ctypes.byref(p), sg, ix, kv, sb, ta, tr, ws, nbytes, _stream(stream))
+    if st != 0 and nbytes < ugbs_workspace_bytes(p):     # the library refuses a short workspace too
+        raise ValueError(f"workspace must hold >= {ugbs_workspace_bytes(p)} bytes")
+    _raise("ugbs_route", st)
 
 
 def ugbs_route_noalloc(p: Problem, sigma, idx_sorted, kv_idx, sigma_bar=None, tau=None, trigger=None,
@@ -252,7 +279,7 @@ def ugbs_route_noalloc(p: Problem, sigma, idx_sorted, kv_idx, sigma_bar=None, ta
     """Stage 4 without a workspace (for callers that cannot allocate): the
     route's sections live in the library's static per-GPU scratch; outputs
     equal ugbs_route's."""
-    import torch
+    torch = _get_torch()
     dev = sigma.device
     sg = _check("sigma", sigma, (p.batch, p.n_heads, p.T), (torch.float32,))
     if (idx_sorted is None) != (kv_idx is None):
@@ -268,17 +295,18 @@ def ugbs_route_noalloc(p: Problem, sigma, idx_sorted, kv_idx, sigma_bar=None, ta
 
 def ugbs_attend(p: Problem, Q, K, V, kv_idx, O, stream=None):
     """Stage 5 (A.10): O [B,H,N,d] = softmax attention over the blocks in kv_idx [B,H,T,W]."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
-    q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
-    k = _check("K", K, (p.batch, p.n_kv_heads, p.seq_len, p.head_dim), bf, dev)
-    v = _check("V", V, (p.batch, p.n_kv_heads, p.seq_len, p.head_dim), bf, dev)
+    B, H, Hkv, N, d = p.batch, p.n_heads, p.n_kv_heads, p.seq_len, p.head_dim
+    q = _check("Q", Q, (B, H, N, d), bf)
+    k = _check("K", K, (B, Hkv, N, d), bf, dev)
+    v = _check("V", V, (B, Hkv, N, d), bf, dev)
     if kv_idx.dim() != 4:
         raise ValueError("kv_idx must be [B,H,T,W]")
     width = int(kv_idx.shape[3])
-    kv = _check("kv_idx", kv_idx, (p.batch, p.n_heads, p.T, width), (torch.int32,), dev)
-    o = _check("O", O, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf, dev)
+    kv = _check("kv_idx", kv_idx, (B, H, N // BLOCK, width), (torch.int32,), dev)
+    o = _check("O", O, (B, H, N, d), bf, dev)
     _raise("ugbs_attend", lib().ugbs_attend(ctypes.byref(p), q, k, v, kv, width, o, _stream(stream)))
 
 
@@ -288,7 +316,7 @@ def ugbs_attend_select(p: Problem, Q, K, V, O, workspace=None, scores=None, trig
     ugbs_route's kv_idx, chosen from the tile scores (`scores` [B,H,T,N_B]
     fp32, or the packed rows ugbs_score_select left in `workspace`) and the
     trigger flags (`trigger` [B,T] uint8, or ugbs_route's in `workspace`)."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
     q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
@@ -299,7 +327,7 @@ def ugbs_attend_select(p: Problem, Q, K, V, O, workspace=None, scores=None, trig
     tr = _opt("trigger", trigger, (p.batch, p.T), (torch.uint8,), dev)
     ws, nbytes = None, 0
     if workspace is not None:
-        ws = _check("workspace", workspace, tuple(workspace.shape), (workspace.dtype,), dev)
+        ws = _check("workspace", workspace, workspace.shape, (workspace.dtype,), dev)
         nbytes = workspace.numel() * workspace.element_size()
     _raise("ugbs_attend_select", lib().ugbs_attend_select(ctypes.byref(p), q, k, v, sc, tr, ws, nbytes, o,
                                                           _stream(stream)))
@@ -313,7 +341,7 @@ def ugbs_select_rows(p: Problem, trigger, bitmap, Q=None, meta=None, row_scores=
     """Per-row selection into tile bitmaps: bitmap [B,H,T,ceil(N_B/32)] int32
     (uint32 words) from the per-row scores of Q against meta (or `row_scores`
     [B,H,N,N_B] fp32) and the trigger flags [B,T] uint8."""
-    import torch
+    torch = _get_torch()
     dev = bitmap.device
     bf = _bf16()
     tr = _check("trigger", trigger, (p.batch, p.T), (torch.uint8,), dev)
@@ -326,7 +354,7 @@ def ugbs_select_rows(p: Problem, trigger, bitmap, Q=None, meta=None, row_scores=
 
 def ugbs_attend_bitmap(p: Problem, Q, K, V, bitmap, O, stream=None):
     """Stage 5 over the blocks set in bitmap [B,H,T,ceil(N_B/32)] (int32 words)."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
     q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
@@ -356,7 +384,7 @@ def _bytes_buf(name, t, n_bytes, dev):
         raise ValueError(f"{name} must hold exactly {n_bytes} bytes")
     if t.device != dev:
         raise ValueError(f"{name} is on {t.device}, expected {dev}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def bai_tile_records(tiles):
@@ -376,7 +404,7 @@ def bai_head_records(heads):
 def ugbs_noise_scale(p: Problem, Q, meta, rough, tau, stream=None):
     """Appendix D step 3: rough [B,H,T] fp64 (per-tile sums of squared
     row-to-row score differences), tau [B,H] fp32."""
-    import torch
+    torch = _get_torch()
     bf = _bf16()
     dev = Q.device
     q = _check("Q", Q, (p.batch, p.n_heads, p.seq_len, p.head_dim), bf)
@@ -391,7 +419,7 @@ def ugbs_bai_tiles(p: Problem, scores, tiles, tau=None, z=None, stream=None):
     fp32 (scores_out layout); tau [B,H] fp32; z [N_B, n_samples] fp32
     (block-major); tiles: device buffer of B*H*T*32 bytes (ugbs_bai_tile
     records)."""
-    import torch
+    torch = _get_torch()
     dev = scores.device
     sc = _check("scores", scores, (p.batch, p.n_heads, p.T, p.NB), (torch.float32,))
     ns = 0 if z is None else int(z.shape[1])
@@ -404,7 +432,7 @@ def ugbs_bai_tiles(p: Problem, scores, tiles, tau=None, z=None, stream=None):
 def ugbs_bai_heads(p: Problem, tiles, tau, n_samples, heads, stream=None):
     """Appendix D per-head aggregates from the tile records; heads: device
     buffer of B*H*160 bytes (ugbs_bai_head records)."""
-    import torch
+    torch = _get_torch()
     dev = tau.device
     ta = _check("tau", tau, (p.batch, p.n_heads), (torch.float32,))
     tl = _bytes_buf("tiles", tiles, p.batch * p.n_heads * p.T * BAI_TILE_BYTES, dev)
