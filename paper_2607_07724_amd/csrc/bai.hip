@@ -25,13 +25,14 @@
 // left-to-right sum.
 #include <math.h>
 
+#include <type_traits>
+
 #include "select_common.h"
 
 namespace ugbs {
 namespace {
 
 constexpr int kBaiUnits = 4;   // query heads of one tile per workgroup (one wave each)
-constexpr int kBaiSlots = UGBS_MAX_BLOCKS_ROWS / 64;
 constexpr int kHeadThreads = 512;
 
 struct TileParams {
@@ -68,6 +69,9 @@ __device__ __forceinline__ float wave_min_f(float x) {
 // m..R'-1, and the count of ranks < R' whose mu beats the outside max.  The
 // draws of a block are read once per workgroup-sample and used by every
 // unit; no cross-lane reduction is needed until the failure counts.
+//
+// SLOTS: 64-candidate slots of the longest row.
+template <int SLOTS>
 __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) {
 #pragma clang fp contract(off)
   extern __shared__ __align__(16) unsigned char smem[];
@@ -94,6 +98,7 @@ __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) 
     }
     return;
   }
+  const int Rp8 = (Rp + 7) & ~7;       // ranks are taken eight at a time
   auto sel_of = [&](int u) { return smem + (size_t)u * P.sel_bytes; };
   auto top_of = [&](int u) { return smem + (size_t)kBaiUnits * P.sel_bytes + (size_t)u * P.top_bytes; };
 
@@ -104,16 +109,18 @@ __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) 
     uint64_t* s_sel = reinterpret_cast<uint64_t*>(sel_of(w));
     const float* src = P.scores + (((size_t)b * s.H + h) * s.T + t) * s.NB + 1;
     const int nslots = (nc + 63) / 64;
-    uint32_t keys[kBaiSlots], pos[kBaiSlots];
+    uint32_t keys[SLOTS], pos[SLOTS];
 #pragma unroll
-    for (int sl = 0; sl < kBaiSlots; ++sl) {
+    for (int sl = 0; sl < SLOTS; ++sl) {
       const int p = 64 * sl + lane;
       keys[sl] = (sl < nslots && p < nc) ? order_key(src[p]) : 0u;
       pos[sl] = (uint32_t)p;
     }
     // sorted top R' + 1 as (key << 32) | ~position, descending
     const int R1 = Rp + 1;
-    select_top<kBaiSlots>(keys, pos, nslots, R1, s_sel, lane);
+    // (eight slots are all counted, the empty ones hold 0: fewer steps than
+    // a branch around each)
+    select_top<SLOTS>(keys, pos, SLOTS <= 8 ? SLOTS : nslots, R1, s_sel, lane);
     int n2 = 2;
     while (n2 < R1) n2 <<= 1;
     for (int p = R1 + lane; p < n2; p += 64) s_sel[p] = 0ull;
@@ -136,17 +143,18 @@ __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) 
     }
     // the top R' in rank order, and the row with them masked out
     float* tv = reinterpret_cast<float*>(top_of(w));
-    int32_t* tp = reinterpret_cast<int32_t*>(tv + Rp);
+    int32_t* tp = reinterpret_cast<int32_t*>(tv + Rp8);
     for (int j = lane; j < Rp; j += 64) {
       const uint64_t e = s_sel[j];
       tv[j] = key_value((uint32_t)(e >> 32));
       tp[j] = (int32_t)(0xffffffffu - (uint32_t)e);
     }
+    if (lane < Rp8 - Rp) tv[Rp + lane] = 0.f, tp[Rp + lane] = 0;   // read, not used
     const uint64_t thr_r = s_sel[Rp - 1];
     wave_lds_sync();  // every read of the sort buffer is done before the row overwrites it
     float* row = reinterpret_cast<float*>(s_sel);
 #pragma unroll
-    for (int sl = 0; sl < kBaiSlots; ++sl) {
+    for (int sl = 0; sl < SLOTS; ++sl) {
       const int p = 64 * sl + lane;
       if (sl < nslots && p < nc) {
         const uint64_t k64 = ((uint64_t)keys[sl] << 32) | (0xffffffffu - (uint32_t)p);
@@ -179,54 +187,79 @@ __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) 
     // candidates outside the top R' (the masked row: the top R' and the
     // padding read -inf, which no draw changes); the next 8 draws are in
     // flight while the current 8 are used
-    float zn[8];
     auto load8 = [&](int p0, float (&zz)[8]) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) zz[i] = zdraw(min(1 + p0 + i, s.NB - 1));
     };
-    load8(0, zn);
-    for (int p = 0; p < nc8; p += 8) {
-      float zz[8];
+    // ALL: every unit is there, so no branch parts the units' LDS reads (one
+    // round trip per step, not one per unit)
+    auto outside = [&](auto all_tag) {
+      constexpr bool ALL = decltype(all_tag)::value;
+      float zn[8];
+      load8(0, zn);
+      for (int p = 0; p < nc8; p += 8) {
+        float zz[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) zz[i] = zn[i];
-      if (p + 8 < nc8) load8(p + 8, zn);
+        for (int i = 0; i < 8; ++i) zz[i] = zn[i];
+        if (p + 8 < nc8) load8(p + 8, zn);
 #pragma unroll
-      for (int u = 0; u < kBaiUnits; ++u) {
-        if (u < n_act) {
-          const float* rw = reinterpret_cast<const float*>(sel_of(u)) + p;
-          const float4 ra = *reinterpret_cast<const float4*>(rw);
-          const float4 rb = *reinterpret_cast<const float4*>(rw + 4);
-          const float rv[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
-          float mx = mx_out[u];
+        for (int u = 0; u < kBaiUnits; ++u) {
+          if (ALL || u < n_act) {
+            const float* rw = reinterpret_cast<const float*>(sel_of(u)) + p;
+            const float4 ra = *reinterpret_cast<const float4*>(rw);
+            const float4 rb = *reinterpret_cast<const float4*>(rw + 4);
+            const float rv[8] = {ra.x, ra.y, ra.z, ra.w, rb.x, rb.y, rb.z, rb.w};
+            float mx = mx_out[u];
 #pragma unroll
-          for (int i = 0; i < 8; ++i) mx = fmaxf(mx, rv[i] + tau_u[u] * zz[i]);
-          mx_out[u] = mx;
+            for (int i = 0; i < 8; ++i) mx = fmaxf(mx, rv[i] + tau_u[u] * zz[i]);
+            mx_out[u] = mx;
+          }
         }
       }
-    }
-    // the top R' in rank order, 8 draws at a time: ranks < m (min, and the
-    // count above the outside max), then ranks m..R'-1 (max, and the count)
+    };
+    if (n_act == kBaiUnits) outside(std::true_type{});
+    else outside(std::false_type{});
+    // the top R' in rank order, 8 draws at a time (the next 8 in flight): ranks
+    // < m (min, and the count above the outside max), then ranks m..R'-1 (max,
+    // and the count).  Groups on one side of the cut carry no test per rank.
 #pragma unroll
     for (int u = 0; u < kBaiUnits; ++u) {
       if (u < n_act) {
         const float* tv = reinterpret_cast<const float*>(top_of(u));
-        const int32_t* tp = reinterpret_cast<const int32_t*>(tv + Rp);
+        const int32_t* tp = reinterpret_cast<const int32_t*>(tv + Rp8);
         const float tu = tau_u[u], mo = mx_out[u];
         float mn_in = __builtin_huge_valf(), mx_mid = -__builtin_huge_valf();
         int above = 0;
+        auto draws = [&](int j0, float (&zz)[8]) {
+          const int4 a = *reinterpret_cast<const int4*>(tp + j0), b = *reinterpret_cast<const int4*>(tp + j0 + 4);
+          const int at[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+          for (int i = 0; i < 8; ++i) zz[i] = zdraw(1 + __builtin_amdgcn_readfirstlane(at[i]));
+        };
+        float nz[8];
+        if (Rp > 0) draws(0, nz);
         for (int j0 = 0; j0 < Rp; j0 += 8) {
-          float zz[8];
+          const float4 a = *reinterpret_cast<const float4*>(tv + j0), b = *reinterpret_cast<const float4*>(tv + j0 + 4);
+          const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+          float x[8];
 #pragma unroll
-          for (int i = 0; i < 8; ++i)
-            zz[i] = zdraw(1 + __builtin_amdgcn_readfirstlane(tp[min(j0 + i, Rp - 1)]));
+          for (int i = 0; i < 8; ++i) x[i] = v[i] + tu * nz[i];
+          if (j0 + 8 < Rp) draws(j0 + 8, nz);
+          if (j0 + 8 <= m) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int j = j0 + i;
-            if (j < Rp) {
-              const float x = tv[j] + tu * zz[i];
-              if (j < m) mn_in = fminf(mn_in, x);
-              else mx_mid = fmaxf(mx_mid, x);
-              above += x > mo;
+            for (int i = 0; i < 8; ++i) mn_in = fminf(mn_in, x[i]), above += x[i] > mo;
+          } else if (j0 >= m && j0 + 8 <= Rp) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mx_mid = fmaxf(mx_mid, x[i]), above += x[i] > mo;
+          } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              const int j = j0 + i;
+              if (j < Rp) {
+                if (j < m) mn_in = fminf(mn_in, x[i]);
+                else mx_mid = fmaxf(mx_mid, x[i]);
+                above += x[i] > mo;
+              }
             }
           }
         }
@@ -516,6 +549,18 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
   *out = hd;
 }
 
+template <int SLOTS>
+hipError_t launch_tiles(const TileParams& P, size_t smem, hipStream_t stream) {
+  if (smem > 65536) {
+    const hipError_t e = hipFuncSetAttribute((const void*)bai_tile_kernel<SLOTS>,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    if (e != hipSuccess) return e;
+  }
+  const int grid = ((P.n_wg + 7) / 8) * 8;
+  bai_tile_kernel<SLOTS><<<grid, 64 * kBaiUnits, smem, stream>>>(P);
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_noise_scale(const Shape& s, const double* rough, float* tau, hipStream_t stream) {
@@ -542,16 +587,12 @@ hipError_t launch_bai_tiles(const Shape& s, const float* scores, const float* ta
   while (n2 < r1 && n2 < s.NB) n2 <<= 1;
   const int sel = 8 * n2 > 4 * (s.NB + 8) ? 8 * n2 : 4 * (s.NB + 8);
   P.sel_bytes = (sel + 15) & ~15;
-  P.top_bytes = (8 * s.W + 15) & ~15;
+  P.top_bytes = 8 * ((s.W + 7) & ~7);   // values and positions, each padded to 8 ranks
   const size_t smem = (size_t)kBaiUnits * (P.sel_bytes + P.top_bytes);
-  if (smem > 65536) {
-    const hipError_t e = hipFuncSetAttribute((const void*)bai_tile_kernel,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e != hipSuccess) return e;
-  }
-  const int grid = ((P.n_wg + 7) / 8) * 8;
-  bai_tile_kernel<<<grid, 64 * kBaiUnits, smem, stream>>>(P);
-  return hipGetLastError();
+  // the kernel for the shortest row that holds N_B, as in the selection
+  if (s.NB <= 8 * 64) return launch_tiles<8>(P, smem, stream);
+  if (s.NB <= 16 * 64) return launch_tiles<16>(P, smem, stream);
+  return launch_tiles<UGBS_MAX_BLOCKS_ROWS / 64>(P, smem, stream);
 }
 
 hipError_t launch_bai_heads(const Shape& s, const ugbs_bai_tile* tiles, const float* tau, int n_s,

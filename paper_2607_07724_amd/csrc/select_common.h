@@ -189,7 +189,7 @@ __device__ __forceinline__ void lds_bitonic_desc(uint64_t* s, int n2, int lane) 
   for (int size = 2; size <= n2; size <<= 1) {
     for (int stride = size >> 1; stride > 0; stride >>= 1) {
       for (int i = lane; i < (n2 >> 1); i += 64) {
-        const int lo = 2 * stride * (i / stride) + (i % stride);
+        const int lo = 2 * i - (i & (stride - 1));   // 2 stride (i / stride) + i % stride
         const int hi = lo + stride;
         const uint64_t x = s[lo], y = s[hi];
         const bool desc = (lo & size) == 0;
