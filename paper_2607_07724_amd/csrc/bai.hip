@@ -70,6 +70,11 @@ __device__ __forceinline__ float wave_min_f(float x) {
 // draws of a block are read once per workgroup-sample and used by every
 // unit; no cross-lane reduction is needed until the failure counts.
 //
+// Bound by vector issue: 2.5 instructions per draw and candidate outside the
+// top R', about 6 per rank inside it.  28/4 heads, 512 blocks, k 32, 256
+// samples: 256 us with 32 slots in every row's code, an LDS wait per unit and
+// step, and a test per rank; 156 us as it is (768 blocks, k 64: 546 / 356).
+//
 // SLOTS: 64-candidate slots of the longest row.
 template <int SLOTS>
 __global__ void __launch_bounds__(64 * kBaiUnits) bai_tile_kernel(TileParams P) {
@@ -350,6 +355,7 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
   __shared__ long long s_redi[kHeadThreads / 64];
   __shared__ float s_pick[3];  // delta2 quantiles 5% / 50%, sigma_(q)
   __shared__ double s_rmean, s_rcv;
+  __shared__ long long s_sum[2];   // failure differences of the routed and of the oracle-best tiles
   const Shape& s = P.s;
   const int bh = blockIdx.x;
   const int tid = threadIdx.x;
@@ -405,8 +411,8 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
   const int i50 = (int)floor(0.5 * (double)(n - 1));
 
   // ---- mean and CV of r: left-to-right fp64 sums in tile order ------------
-  // One thread of the last wave, whose tiles come last in the rank counting
-  // below; 16 values are read ahead of their dependent adds (one LDS round trip
+  // One thread of the last wave, beside the selections of the first four; 16
+  // values are read ahead of their dependent adds (one LDS round trip
   // per add took 30 us of the kernel's 66 at 448 tiles).
   if (tid == kHeadThreads - 1) {
     auto in_order = [&](auto&& term) {
@@ -428,41 +434,56 @@ __global__ void __launch_bounds__(kHeadThreads) bai_head_kernel(HeadParams P) {
     s_rcv = (mean != 0.0) ? __dsqrt_rn(var) / mean : nan;
   }
 
-  // ---- order statistics by rank counting ----------------------------------
-  // rank of tile i among the spacings (value, then tile order) and among the
-  // sigmas (value, then tile order: the router takes the nq smallest, lower
-  // tile first on ties); failure differences d = fail_k - fail_rk ranked
-  // descending for the oracle-best set
-  long long top_d = 0, rsig_d = 0;
-  for (int i = tid; i < n; i += kHeadThreads) {
-    const float di = s_d2[i], si = s_sig[i];
-    const int ki = s_dk[i];
-    int rd = 0, rs = 0, rk = 0;
-    // four tiles a step (the entries past n are read but not counted)
-    for (int j0 = 0; j0 < n; j0 += 4) {
-      const float4 d4 = *reinterpret_cast<const float4*>(s_d2 + j0);
-      const float4 s4 = *reinterpret_cast<const float4*>(s_sig + j0);
-      const int4 k4 = *reinterpret_cast<const int4*>(s_dk + j0);
-      const float dv[4] = {d4.x, d4.y, d4.z, d4.w}, sv[4] = {s4.x, s4.y, s4.z, s4.w};
-      const int kv[4] = {k4.x, k4.y, k4.z, k4.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int j = j0 + e;
-        const bool in = j < n, before = j < i;
-        rd += in && ((dv[e] < di) || (dv[e] == di && before));
-        rs += in && ((sv[e] < si) || (sv[e] == si && before));
-        rk += in && ((kv[e] > ki) || (kv[e] == ki && before));
-      }
+  // ---- order statistics, one wave each ------------------------------------
+  // Waves 0 and 1: the 5% and 50% spacings.  Wave 2: the nq tiles of smallest
+  // sigma (value, then tile order: the router takes lower tiles first on ties).
+  // Wave 3: the oracle-best nq tiles, by failure difference d = fail_k - fail_rk
+  // descending.  Each is a radix descent over keys in registers.  The kernel,
+  // with every tile's rank counted (n^2 steps) / as it is: 57 / 16 us at 512
+  // blocks, 137 / 22 at 768, 467 / 32 at 1536.
+  // A NaN counts as larger than every number, and its tile is among the routed.
+  const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (w < 4) {
+    auto key_of = [&](int i) -> uint32_t {
+      if (w == 3) return ~((uint32_t)s_dk[i] ^ 0x80000000u);
+      const float x = w == 2 ? s_sig[i] : s_d2[i];
+      return __builtin_isnan(x) ? 0xffffffffu : order_key(x);
+    };
+    const int rank = w == 0 ? i05 : (w == 1 ? i50 : nq - 1);
+    uint32_t thr = 0u;
+    if (rank >= 0) thr = nth_smallest<UGBS_MAX_BLOCKS_ROWS / 64>(key_of, n, rank + 1, lane);
+    if (w < 3) {
+      if (lane == 0) s_pick[w] = key_value(thr);
     }
-    if (rd == i05) s_pick[0] = di;
-    if (rd == i50) s_pick[1] = di;
-    if (nq > 0 && rs == nq - 1) s_pick[2] = si;
-    if (rk < nq) top_d += ki;
-    if (rs < nq) rsig_d += ki;
+    if (w >= 2) {
+      // sum of d over the nq first tiles: below the threshold, and the first
+      // ones at it
+      long long sum = 0;
+      int n_below = 0;
+      if (nq > 0) {
+        for (int i = lane; i < n; i += 64) {
+          const uint32_t k = key_of(i);
+          n_below += k < thr;
+          if (k < thr || k == 0xffffffffu) sum += s_dk[i];
+        }
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) n_below += __shfl_xor(n_below, o);
+        int need = thr == 0xffffffffu ? 0 : nq - n_below;
+        for (int i0 = 0; i0 < n && need > 0; i0 += 64) {
+          const int i = i0 + lane;
+          const bool eq = i < n && key_of(i) == thr;
+          const uint64_t mk = __ballot(eq);
+          if (eq && lanes_below(mk) < need) sum += s_dk[i];
+          need -= (int)__popcll(mk);
+        }
+      }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
+      if (lane == 0) s_sum[w - 2] = sum;
+    }
   }
-  const long long top = block_sum_i(top_d, s_redi);
-  const long long rsig = block_sum_i(rsig_d, s_redi);
-  // (block_sum_i synchronises, so s_pick, s_rmean and s_rcv are visible)
+  __syncthreads();
+  const long long rsig = s_sum[0], top = s_sum[1];
   const float p05 = s_pick[0];
   const double r_mean = s_rmean, r_cv = s_rcv;
   const double sq = nq > 0 ? (double)s_pick[2] : nan;
@@ -589,7 +610,8 @@ hipError_t launch_bai_tiles(const Shape& s, const float* scores, const float* ta
   P.sel_bytes = (sel + 15) & ~15;
   P.top_bytes = 8 * ((s.W + 7) & ~7);   // values and positions, each padded to 8 ranks
   const size_t smem = (size_t)kBaiUnits * (P.sel_bytes + P.top_bytes);
-  // the kernel for the shortest row that holds N_B, as in the selection
+  // the kernel for the shortest row that holds N_B: phase 1 runs through all of
+  // its slots' code (200 blocks, 28 heads: 74 -> 48 us with this and the rest above)
   if (s.NB <= 8 * 64) return launch_tiles<8>(P, smem, stream);
   if (s.NB <= 16 * 64) return launch_tiles<16>(P, smem, stream);
   return launch_tiles<UGBS_MAX_BLOCKS_ROWS / 64>(P, smem, stream);

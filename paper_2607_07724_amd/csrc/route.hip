@@ -11,7 +11,7 @@
 // computed on the host, so no device-to-host synchronisation is needed.
 #include <mutex>
 
-#include "ugbs_internal.h"
+#include "select_common.h"
 
 namespace ugbs {
 namespace {
@@ -37,46 +37,6 @@ struct RouteParams {
   float* ws_tau;
   uint8_t* ws_trigger;
 };
-
-// The n-th smallest (n >= 1) of `count` keys in LDS, by one wave: a
-// most-significant-bit-first radix descent over keys in registers, counting
-// with ballots, that ends once exactly n keys are at or below the candidate.
-__device__ __forceinline__ uint32_t nth_smallest(const uint32_t* keys, int count, int n, int lane) {
-  constexpr int kSlots = UGBS_MAX_BLOCKS / 64, kGroup = 8;
-  const int nslots = (count + 63) / 64;
-  uint32_t key[kSlots];
-#pragma unroll
-  for (int g = 0; g < kSlots; g += kGroup)
-    if (g < nslots) {
-#pragma unroll
-      for (int j = g; j < g + kGroup; ++j) key[j] = 64 * j + lane < count ? keys[64 * j + lane] : 0xffffffffu;
-    }
-  uint32_t ans = 0;
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t c = ans | ((1u << bit) - 1u);
-    int cnt = 0;
-#pragma unroll
-    for (int g = 0; g < kSlots; g += kGroup)
-      if (g < nslots) {
-#pragma unroll
-        for (int j = g; j < g + kGroup; ++j) cnt += (int)__popcll(__ballot(key[j] <= c));
-      }
-    if (cnt == n) {                       // the answer is the largest key <= c
-      uint32_t m = 0;
-#pragma unroll
-      for (int g = 0; g < kSlots; g += kGroup)
-        if (g < nslots) {
-#pragma unroll
-          for (int j = g; j < g + kGroup; ++j) m = max(m, key[j] <= c ? key[j] : 0u);
-        }
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
-      return m;
-    }
-    if (cnt < n) ans |= 1u << bit;
-  }
-  return ans;
-}
 
 template <int V>
 __device__ __forceinline__ void load_slots(const int32_t* p, int32_t (&v)[V]) {
@@ -139,7 +99,7 @@ __global__ void __launch_bounds__(kStatsThreads) route_kernel(RouteParams P, int
   }
   __syncthreads();
   if (wv == 0) {
-    const float tau = P.n_trig > 0 ? __uint_as_float(nth_smallest(s_key, s.T, P.n_trig, lane)) : -1.0f;
+    const float tau = P.n_trig > 0 ? __uint_as_float(nth_smallest<UGBS_MAX_BLOCKS / 64>([&](int i) { return s_key[i]; }, s.T, P.n_trig, lane)) : -1.0f;
     if (lane == 0) s_tau = tau;
   }
   __syncthreads();

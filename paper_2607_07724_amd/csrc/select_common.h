@@ -109,6 +109,49 @@ __device__ __forceinline__ uint32_t kth_largest(const uint32_t (&key)[S], int ns
   return thr;
 }
 
+// The n-th smallest (n >= 1) of the `count` keys key_of(0..count-1), at most 64
+// SLOTS, by one wave: a most-significant-bit-first radix descent over keys in
+// registers, counting with ballots, that ends once exactly n keys are at or
+// below the candidate.  0xffffffff if fewer than n keys are smaller than that.
+template <int SLOTS, typename Key>
+__device__ __forceinline__ uint32_t nth_smallest(Key&& key_of, int count, int n, int lane) {
+  constexpr int kSlots = SLOTS, kGroup = 8;
+  static_assert(SLOTS % kGroup == 0, "whole groups");
+  const int nslots = (count + 63) / 64;
+  uint32_t key[kSlots];
+#pragma unroll
+  for (int g = 0; g < kSlots; g += kGroup)
+    if (g < nslots) {
+#pragma unroll
+      for (int j = g; j < g + kGroup; ++j) key[j] = 64 * j + lane < count ? key_of(64 * j + lane) : 0xffffffffu;
+    }
+  uint32_t ans = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = ans | ((1u << bit) - 1u);
+    int cnt = 0;
+#pragma unroll
+    for (int g = 0; g < kSlots; g += kGroup)
+      if (g < nslots) {
+#pragma unroll
+        for (int j = g; j < g + kGroup; ++j) cnt += (int)__popcll(__ballot(key[j] <= c));
+      }
+    if (cnt == n) {                       // the answer is the largest key <= c
+      uint32_t m = 0;
+#pragma unroll
+      for (int g = 0; g < kSlots; g += kGroup)
+        if (g < nslots) {
+#pragma unroll
+          for (int j = g; j < g + kGroup; ++j) m = max(m, key[j] <= c ? key[j] : 0u);
+        }
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+      return m;
+    }
+    if (cnt < n) ans |= 1u << bit;
+  }
+  return ans;
+}
+
 // R largest of the keys held in key[0..nslots) (0 = empty; entries in
 // position order slot by slot, lane by lane), written to s_sel[0..R) as
 // (key << 32) | ~position, unsorted: the R-th largest key thr comes from
