@@ -233,32 +233,32 @@ attend_keys_kernel(AttnParams P) {
     for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
       for (int rt = 0; rt < 4; ++rt) sc[kt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-          const uint16_t* vsrc = Vh + (size_t)cur * kBlock * D;
-          const uint32_t kr = here(ka), vo = here(voff);
-          constexpr int NR = 2 * KS;
-          bf16x8 ak[NR], lq[KS][4];
-          auto k_op = [&](int j) {
-            if ((j & 1) == 0) {
-    #pragma unroll
-              for (int rt = QR; rt < 4; ++rt)
-                lq[j >> 1][rt] = as_bf16x8(*reinterpret_cast<const uint4*>(s_q + (kr ^ (uint32_t)(64 * (j >> 1))) +
-                                                                           (rt - QR) * 16 * L::kRow));
-            }
-            ak[j] = as_bf16x8(*reinterpret_cast<const uint4*>(tk + (kr ^ (uint32_t)(64 * (j >> 1))) + (j & 1) * 16 * L::kRow));
-          };
-    #pragma unroll
-          for (int j = 0; j < AHEAD; ++j) k_op(j);
-    #pragma unroll
-          for (int j = 0; j < NR; ++j) {
-            if (j + AHEAD < NR) k_op(j + AHEAD);
-            __builtin_amdgcn_sched_barrier(0);
-    #pragma unroll
-            for (int rt = 0; rt < 4; ++rt)
-              sc[j & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[j], rt < QR ? bq[rt < QR ? rt : 0][j >> 1] : lq[j >> 1][rt],
-                                                                      sc[j & 1][rt], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (LOAD_V) load_v(vsrc, vo, j);
-          }
+    const uint16_t* vsrc = Vh + (size_t)cur * kBlock * D;
+    const uint32_t kr = here(ka), vo = here(voff);
+    constexpr int NR = 2 * KS;
+    bf16x8 ak[NR], lq[KS][4];
+    auto k_op = [&](int j) {
+      if ((j & 1) == 0) {
+#pragma unroll
+        for (int rt = QR; rt < 4; ++rt)
+          lq[j >> 1][rt] = as_bf16x8(*reinterpret_cast<const uint4*>(s_q + (kr ^ (uint32_t)(64 * (j >> 1))) +
+                                                                     (rt - QR) * 16 * L::kRow));
+      }
+      ak[j] = as_bf16x8(*reinterpret_cast<const uint4*>(tk + (kr ^ (uint32_t)(64 * (j >> 1))) + (j & 1) * 16 * L::kRow));
+    };
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) k_op(j);
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+      if (j + AHEAD < NR) k_op(j + AHEAD);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int rt = 0; rt < 4; ++rt)
+        sc[j & 1][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ak[j], rt < QR ? bq[rt < QR ? rt : 0][j >> 1] : lq[j >> 1][rt],
+                                                                sc[j & 1][rt], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (LOAD_V) load_v(vsrc, vo, j);
+    }
     static_assert(NR == L::kLoads, "one V load per K operand");
   };
 
