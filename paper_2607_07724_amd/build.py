@@ -64,9 +64,9 @@ def _tool(name):
     return path if os.path.exists(path) else name
 
 
-def device_disassembly(obj: str) -> str:
-    """Disassembly of the gfx950 code object embedded in a host object built
-    here (its .hip_fatbin section, unbundled); empty for an object without
+def _device_tool(obj: str, *cmd: str) -> str:
+    """Output of a tool run on the gfx950 code object embedded in a host object
+    built here (its .hip_fatbin section, unbundled); empty for an object without
     device code."""
     sec = subprocess.run([_tool("llvm-readelf"), "-S", obj], check=True, capture_output=True, text=True)
     if ".hip_fatbin" not in sec.stdout:
@@ -79,8 +79,17 @@ def device_disassembly(obj: str) -> str:
         subprocess.run([_tool("clang-offload-bundler"), "--unbundle", "--type=o", f"--input={fat}",
                         f"--targets=hipv4-amdgcn-amd-amdhsa--{ARCH}", f"--output={co}"],
                        check=True, capture_output=True)
-        r = subprocess.run([_tool("llvm-objdump"), "-d", co], check=True, capture_output=True, text=True)
+        r = subprocess.run([_tool(cmd[0]), *cmd[1:], co], check=True, capture_output=True, text=True)
         return r.stdout
+
+
+def device_disassembly(obj: str) -> str:
+    return _device_tool(obj, "llvm-objdump", "-d")
+
+
+def device_notes(obj: str) -> str:
+    """The code object's metadata: each kernel's registers, spills and static LDS."""
+    return _device_tool(obj, "llvm-readelf", "--notes")
 
 
 def check_no_packed_fp32(obj: str) -> int:

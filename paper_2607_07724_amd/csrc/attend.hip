@@ -1,12 +1,13 @@
-// Stage 5 at d 256 (attend_keys.hip: d 64 and 128): block-sparse causal
+// Stage 5 at d 256, and at d 128 where the walk is bound beyond the L2 (see
+// coupled_walk; attend_keys.hip: d 64 and the rest of d 128): block-sparse causal
 // attention over kv_idx, a bitmap, or an in-kernel selection (A.10; Eq. (Attn)).
 //
 // One workgroup per (batch, query head, Q-tile) unit: four waves of 16 query
-// rows; wave w owns rows 16 w .. 16 w + 15 of the tile.  The tile's kept blocks
-// are first turned into an ascending list of distinct blocks in 0..t (so the
-// diagonal block comes last), then visited one by one.  (Splitting the keys
-// over the waves instead, as at d 64 and 128, needs all 64 rows' accumulators
-// in every wave: 256 registers at this d.)
+// rows (d 128: two of 32); a wave owns its rows for every key of a block.  The
+// tile's kept blocks are first turned into an ascending list of distinct blocks
+// in 0..t (so the diagonal block comes last), then visited one by one.
+// (Splitting the keys over the waves instead, as attend_keys.hip does, needs all
+// 64 rows' accumulators in every wave: 256 registers at d 256.)
 //
 // Staging.  K and V blocks (64 keys x d, bf16) go global -> LDS with
 // direct-to-LDS loads (global_load_lds_dwordx4: no registers, no VALU).
@@ -40,26 +41,28 @@
 namespace ugbs {
 namespace {
 
-constexpr int D = 256;
-constexpr int NWV = 4;            // waves per unit, 16 query rows each: two waves fit on a SIMD
-constexpr int kThreads = 64 * NWV;
-constexpr int RT = 1;             // 16-row tiles per wave
-constexpr int RPW = 16 * RT;      // query rows per wave
-
-struct Tile : TileGeom<D> {
-  static constexpr int kLoadsPerWave = TileGeom<D>::kLoads / NWV;
+// Waves per unit and 16-row tiles per wave: d 128 runs two waves of 32 query
+// rows, d 256 four waves of 16 (half the accumulators per wave).  Two waves per
+// SIMD at both.
+template <int D>
+struct Geo {
+  static constexpr int RT = D > 128 ? 1 : 2;   // 16-row tiles per wave
+  static constexpr int NWV = 4 / RT;           // waves per unit (64 rows)
+  static constexpr int kThreads = 64 * NWV;
 };
 
-template <int MODE>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <int D, int MODE>
+__global__ void __launch_bounds__(Geo<D>::kThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 attend_kernel(AttnParams P) {
-  using L = Tile;
+  using L = TileGeom<D>;
+  constexpr int NWV = Geo<D>::NWV, kThreads = Geo<D>::kThreads;
+  constexpr int RT = Geo<D>::RT;
+  constexpr int RPW = 16 * RT;    // query rows per wave
   constexpr int KS = D / 32;      // k-steps of QK^T
   constexpr int DT = D / 16;      // 16-channel tiles of O^T
-  constexpr int NW = L::kLoadsPerWave;
   __shared__ __align__(16) uint16_t s_k[L::kElems];
   __shared__ __align__(16) uint16_t s_v[L::kElems];
-  extern __shared__ int32_t s_list[];              // list_bytes
+  extern __shared__ uint16_t s_list[];              // list_bytes
   __shared__ uint32_t s_bits[UGBS_MAX_BLOCKS / 32];
   __shared__ int s_n, s_below;
 
@@ -131,14 +134,25 @@ attend_kernel(AttnParams P) {
   const uint16_t* Vh = P.V + ((size_t)u.b * s.Hkv + kvh) * s.N * D;
   const uint32_t k_lds = __builtin_amdgcn_readfirstlane(lds_addr(s_k));
   const uint32_t v_lds = __builtin_amdgcn_readfirstlane(lds_addr(s_v));
-  // every wave issues its share of a tile's loads (one issuer per tile would
-  // need more offset registers than this kernel has)
-  FetchPlanT<D, false, NWV> kplan;
-  FetchPlanT<D, true, NWV> vplan;
-  kplan.init(lane, w);
-  vplan.init(lane, w);
-  auto fetch_k = [&](int b) { kplan.fetch(Kh + (size_t)b * Tile::kElems, k_lds, w); };
-  auto fetch_v = [&](int b) { vplan.fetch(Vh + (size_t)b * Tile::kElems, v_lds, w); };
+  // Who issues a tile's 1 KiB loads.  At d 128 the first wave issues all of a K
+  // tile and the last wave all of a V tile, so while one wave waits for the
+  // texture unit to accept its loads the other keeps computing (1-2% faster at
+  // 32K-128K than each wave issuing half of every tile, same output bits).  At
+  // d 256 each wave issues its share: one issuer would need more offset
+  // registers than that kernel has.
+  constexpr bool kSplitIssue = D <= 128;
+  constexpr int kIssuers = kSplitIssue ? 1 : NWV;
+  FetchPlanT<D, false, kIssuers> kplan;
+  FetchPlanT<D, true, kIssuers> vplan;
+  const int iw = kSplitIssue ? 0 : w;             // index within the issuing waves
+  kplan.init(lane, iw);
+  vplan.init(lane, iw);
+  auto fetch_k = [&](int b) {
+    if (!kSplitIssue || w == 0) kplan.fetch(Kh + (size_t)b * L::kElems, k_lds, iw);
+  };
+  auto fetch_v = [&](int b) {
+    if (!kSplitIssue || w == NWV - 1) vplan.fetch(Vh + (size_t)b * L::kElems, v_lds, iw);
+  };
 
   f32x4 acc_o[DT][RT];
 #pragma unroll
@@ -152,7 +166,7 @@ attend_kernel(AttnParams P) {
     l_run[rt] = 0.f;
   }
 
-  // S^T = K Q^T : [64 keys x 32 rows] per wave, K from LDS
+  // S^T = K Q^T : [64 keys x 16 RT rows] per wave, K from LDS
   auto compute_s = [&](f32x4 (&sc)[4][RT]) {
 #pragma unroll
     for (int kt = 0; kt < 4; ++kt)
@@ -183,7 +197,11 @@ attend_kernel(AttnParams P) {
   fetch_v(blk);
   f32x4 sc[4][RT];
   // K0 landed (V0 may still be in flight)
-  wait_vmcnt<NW>();
+  if constexpr (kSplitIssue) {
+    if (w == 0) wait_vmcnt<0>();
+  } else {
+    wait_vmcnt<L::kLoads / NWV>();
+  }
   lds_barrier();
   compute_s(sc);
   wait_lgkm0();
@@ -213,7 +231,7 @@ attend_kernel(AttnParams P) {
     __builtin_amdgcn_s_setprio(1);       // matrix-core phases issue ahead of other waves' fetch phases
     compute_s(sn);
 
-    // online softmax of S(it) (base 2); lane holds row (32w + 16rt + c16),
+    // online softmax of S(it) (base 2); lane holds row (RPW w + 16rt + c16),
     // keys 16kt + 4g + i.  The reference max m_run only moves when a row max
     // exceeds it by more than 2^8, so p <= 256 and O is rescaled rarely.
     if constexpr (MASK) {
@@ -261,8 +279,8 @@ attend_kernel(AttnParams P) {
       }
     }
     // interleave, in two halves: the K-operand reads, then one MFMA of
-    // S(it+1) per few softmax VALU instructions
-    constexpr int kHalfReads = 2 * KS, kHalfMfma = 2 * KS * RT, kVpm = 2;
+    // S(it+1) per few softmax VALU instructions (8 reads, 16 x (1 + 5) at d 128)
+    constexpr int kHalfReads = 2 * KS, kHalfMfma = 2 * KS * RT, kVpm = RT == 2 ? 5 : 2;
 #pragma unroll
     for (int half = 0; half < 2; ++half) {
       __builtin_amdgcn_sched_group_barrier(0x100, kHalfReads, 0);
@@ -356,13 +374,45 @@ attend_kernel(AttnParams P) {
   }
 }
 
-template <int MODE>
+template <int D, int MODE>
 hipError_t launch_t(AttnParams P, hipStream_t stream) {
   const size_t smem = list_bytes(P);
-  const int grid = P.order.grid;
-  P.conc = xcd_concurrency<attend_kernel<MODE>, true>(kThreads, smem);
-  attend_kernel<MODE><<<grid, kThreads, smem, stream>>>(P);
+  constexpr auto kernel = attend_kernel<D, MODE>;
+  P.conc = xcd_concurrency<kernel, (D > 128)>(Geo<D>::kThreads, smem);
+  kernel<<<P.order.grid, Geo<D>::kThreads, smem, stream>>>(P);
   return hipGetLastError();
+}
+
+// d 128 lists: true where the units' walks are bound by what misses the L2.  The
+// kernel here keeps a unit's waves on one block between barriers, so a unit that
+// has to wait for a block waits whole, the units behind it on that XCD catch up,
+// and the blocks they share are fetched once more often: L2 hits .59 against .45
+// of attend_keys.hip's independent waves at 2048 blocks (14/2 heads, k 256, q
+// 0.1), with 7 TB/s beyond the L2 either way.  Where the L2 isn't the bound those
+// waves are faster.  Two things take a list there: long sequences, whose range
+// of blocks is far larger than an L2 (4 MB: 128 blocks of K and V), and many
+// blocks per list; K-mean scores, which spread a tile's blocks more than the
+// Quest bound does, at any budget.  Measured (ms, here / attend_keys.hip):
+//   Quest, q 0.1    1500 blocks   k 256, 14/2 heads   12.1 / 11.1
+//                   2048          k 64, 32/8          10.6 / 10.0    k 256, 14/2   17.5 / 19.2
+//                   3000          k 64, 32/8          16.3 / 16.0    k 96, 14/2    10.4 / 11.0
+//                   4096          k 64, 32/8          23.5 / 23.5    k 128, 14/2   22.3 / 22.8
+//   K-mean, q 0.1   1200          k 64, 14/2          2.79 / 2.68
+//                   1500          k 64, 14/2          3.68 / 3.99
+//                   2048          k 33, 14/2          3.06 / 3.15    k 256, 14/2   21.9 / 24.3
+//   every block     1400, 32/8    75 / 75      2048   171 / 211     4096, 16/4   391 / 476
+// The choice depends on the problem and the list's width alone, so ugbs_attend
+// and ugbs_attend_select take the same kernel and agree bit for bit.
+inline bool coupled_walk(const AttnParams& P) {
+  return P.s.d == 128 && P.s.NB >= 1408 && (P.s.backbone == UGBS_KMEAN || P.expected * P.s.NB >= 300000.0);
+}
+
+template <int MODE>
+hipError_t launch_mode(const AttnParams& P, hipStream_t stream) {
+  if (P.s.d == 256) return launch_t<256, MODE>(P, stream);
+  if constexpr (MODE != kBitmap)
+    if (coupled_walk(P)) return launch_t<128, MODE>(P, stream);
+  return launch_attend_keys(P, MODE, stream);
 }
 
 }  // namespace
@@ -381,7 +431,7 @@ hipError_t launch_attend(const Shape& s, const uint16_t* Q, const uint16_t* K,
   P.kv_width = kv_width;
   P.expected = expected_blocks(s, kv_width);
   P.scale_log2 = s.scale * 1.4426950408889634f;
-  return s.d == 256 ? launch_t<kLists>(P, stream) : launch_attend_keys(P, kLists, stream);
+  return launch_mode<kLists>(P, stream);
 }
 
 hipError_t launch_attend_select(const Shape& s, const uint16_t* Q, const uint16_t* K,
@@ -402,9 +452,7 @@ hipError_t launch_attend_select(const Shape& s, const uint16_t* Q, const uint16_
   P.sel_scores = scores;
   P.sel_packed = ws ? reinterpret_cast<const float*>(ws + ws_scores_off(s)) : nullptr;
   P.sel_trigger = trigger ? trigger : ws + ws_trigger_off(s);
-  const bool wide = s.NB > 32 * 64;
-  if (s.d != 256) return launch_attend_keys(P, wide ? kSelectWide : kSelect, stream);
-  return wide ? launch_t<kSelectWide>(P, stream) : launch_t<kSelect>(P, stream);
+  return s.NB > 32 * 64 ? launch_mode<kSelectWide>(P, stream) : launch_mode<kSelect>(P, stream);
 }
 
 hipError_t launch_attend_bitmap(const Shape& s, const uint16_t* Q, const uint16_t* K,
@@ -422,7 +470,7 @@ hipError_t launch_attend_bitmap(const Shape& s, const uint16_t* Q, const uint16_
   P.scale_log2 = s.scale * 1.4426950408889634f;
   P.bitmap = bitmap;
   P.nw = (s.NB + 31) / 32;
-  return s.d == 256 ? launch_t<kBitmap>(P, stream) : launch_attend_keys(P, kBitmap, stream);
+  return launch_mode<kBitmap>(P, stream);
 }
 
 }  // namespace ugbs

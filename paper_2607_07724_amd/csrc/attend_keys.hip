@@ -105,7 +105,7 @@ attend_keys_kernel(AttnParams P) {
   static_assert(sizeof(float2) * 2 * kBlock >= UGBS_MAX_BLOCKS / 8, "the bitmap fits");
   uint32_t* const s_bits = reinterpret_cast<uint32_t*>(s_ml);
   __shared__ __align__(16) unsigned char s_q[QR < 4 ? (4 - QR) * 16 * L::kRow : 16];   // query tiles QR..3
-  extern __shared__ int32_t s_list[];              // list_bytes
+  extern __shared__ uint16_t s_list[];              // list_bytes
   __shared__ int s_n, s_below;
 
   const Shape& s = P.s;

@@ -110,7 +110,7 @@ __device__ __forceinline__ bool attend_unit(const Shape& s, const AttendOrder& o
 template <int MODE, int NWV>
 __device__ __forceinline__ void build_list(const AttnParams& P, const Unit& u, size_t rowid, int start_blk, int w,
                                            int lane, uint64_t* surv, uint32_t* top, uint32_t* s_bits,
-                                           int32_t* s_list, int* s_n, int* s_below) {
+                                           uint16_t* s_list, int* s_n, int* s_below) {
   const Shape& s = P.s;
   // Selection modes, shared part: the unit's waves split the candidate
   // loads, the keys, each lane's top-3 pre-filter and the survivor
@@ -322,7 +322,7 @@ __device__ __forceinline__ void build_list(const AttnParams& P, const Unit& u, s
       const int blk = base + lane;
       const bool on = blk <= u.t && ((s_bits[blk >> 5] >> (blk & 31)) & 1u);
       const uint64_t m = __ballot(on);
-      if (on) s_list[n + lanes_below(m)] = blk;
+      if (on) s_list[n + lanes_below(m)] = (uint16_t)blk;
       n += __popcll(m);
       below += __popcll(__ballot(on && blk < start_blk));
     }
@@ -340,11 +340,13 @@ inline double expected_blocks(const Shape& s, int width) {
   return e < s.NB ? e : s.NB;
 }
 
-// LDS of a unit's list: at most kv_width distinct blocks, and at most N_B.  (The
-// same for lists of 2k slots and for the in-kernel selection, so both run at
-// the same occupancy and visit the blocks in the same order.)
+// LDS of a unit's list: at most kv_width distinct blocks, and at most N_B, 16 bits
+// each (long lists cost resident units).  The same for lists of 2k slots and for
+// the in-kernel selection, so both run at the same occupancy and visit the
+// blocks in the same order.
+static_assert(UGBS_MAX_BLOCKS <= 65536, "16-bit list entries");
 inline size_t list_bytes(const AttnParams& P) {
-  return sizeof(int32_t) * (size_t)(P.kv_width < P.s.NB ? P.kv_width : P.s.NB);
+  return sizeof(uint16_t) * (size_t)(P.kv_width < P.s.NB ? P.kv_width : P.s.NB);
 }
 
 // Workgroups of an attention kernel resident at once on one XCD, for the given
@@ -365,7 +367,7 @@ int xcd_concurrency(int threads, size_t smem) {
   }
   if (RAISE)
     (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sizeof(int32_t) * UGBS_MAX_KV_WIDTH);
+                              (int)sizeof(uint16_t) * UGBS_MAX_KV_WIDTH);
   int per_cu = 0, n_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, smem) != hipSuccess) per_cu = 1;
   if (dev < 0 || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 8;

@@ -1,0 +1,58 @@
+"""The launches the library makes, recorded on the CPU (launch_probe.py): which
+attention kernel a call takes, and what its LDS leaves resident."""
+import pytest
+
+import paper_2607_07724_amd as ugbs
+from launch_probe import launches, static_lds, workgroups_per_cu
+
+make = ugbs.Problem.make
+
+
+def waves_per_cu(x):
+    return workgroups_per_cu(x) * x["block"] // 64
+
+
+@pytest.mark.parametrize("d", [64, 128, 256])
+def test_lists_of_every_length_leave_the_simds_full(d):
+    """Two waves per SIMD (three at d 64, which its registers allow) whatever
+    the list's length: entries of 16 bits, at most one per block.  (The coupled
+    kernel at d 128 holds three units of two waves where a list has more than
+    3836 entries.)"""
+    calls = []
+    for NB in (64, 767, 1024, 1407, 1408, 2048, 2559, 4096):
+        p = make(1, 8, 2, 64 * NB, d, 64, 0.1, ugbs.QUEST)
+        calls += [("attend", p, W) for W in (1, 128, 766, 767, 1024, 4096)] + [("attend_bitmap", p)]
+    for st, xs in launches(calls):
+        assert st == 0 and len(xs) == 1
+        x = xs[0]
+        coupled = x["kernel"].startswith("attend_kernel<128") and x["dynamic"] > 2 * 3836
+        assert waves_per_cu(x) >= (12 if d == 64 else 6 if coupled else 8), x
+        assert x["dynamic"] <= 2 * 4096
+
+
+def test_long_walks_at_d128_keep_their_waves_coupled():
+    def kernel(NB, backbone, k, W=None, H=28, Hkv=4):
+        p = make(1, H, Hkv, 64 * NB, 128, k, 0.1, backbone)
+        return launches([("attend", p, W or 2 * k)])[0][1][0]["kernel"]
+    for NB in (1408, 2048, 4096):                     # every visible block listed
+        assert kernel(NB, ugbs.QUEST, 64, NB) == "attend_kernel<128, 0>"
+    assert kernel(2048, ugbs.KMEAN, 64) == "attend_kernel<128, 0>"
+    assert kernel(2048, ugbs.QUEST, 256) == "attend_kernel<128, 0>"
+    for NB, backbone, k in ((1407, ugbs.KMEAN, 64), (1024, ugbs.KMEAN, 500), (2048, ugbs.QUEST, 64), (4096, ugbs.QUEST, 64)):
+        assert kernel(NB, backbone, k).startswith("attend_keys_kernel<128, 0,")
+
+
+def test_lists_and_selection_take_the_same_kernel():
+    """The two entry points agree bit for bit, so they have to split a unit's
+    work alike: same kernel, same block, same LDS for the list."""
+    probs = [make(B, H, Hkv, 64 * NB, d, k, q, bb, rho=rho)
+             for B, H, Hkv in ((1, 4, 1), (1, 28, 4), (2, 8, 2)) for NB in (16, 100, 700, 1407, 1408, 2049, 4096)
+             for d in (64, 128, 256) for k, q, bb, rho in ((4, 0.25, ugbs.KMEAN, 2), (64, 0.1, ugbs.QUEST, 2),
+                                                            (400, 0.4, ugbs.QUEST, 4))]
+    a = launches([("attend", p, p.W) for p in probs])
+    b = launches([("attend_select", p) for p in probs])
+    for p, (_, (x,)), (_, (y,)) in zip(probs, a, b):
+        form = lambda z: z["kernel"].replace(", 0", ", m").replace(", 1", ", m").replace(", 3", ", m")
+        assert form(x) == form(y), p
+        assert (x["block"], x["grid"], x["dynamic"]) == (y["block"], y["grid"], y["dynamic"]), p
+        assert static_lds()[x["kernel"]] == static_lds()[y["kernel"]], p
