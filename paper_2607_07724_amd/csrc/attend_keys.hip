@@ -122,9 +122,11 @@ attend_keys_kernel(AttnParams P) {
   // wraps around (the diagonal block stays last).  Workgroups follow each
   // other on an XCD in the order of j, conc of them at a time, so the ones
   // resident together sweep the key range in step and blocks they share
-  // stay in that XCD's L2.  Bitmaps: a period of 1 conc.
+  // stay in that XCD's L2.  Bitmaps with four waves: a period of 1 conc (1600
+  // blocks, 16/4 heads: 34.6 ms for 36.4); with two, 2 conc as for lists (512
+  // blocks, 28/4 heads: 5.6 ms for 6.2).
   const int j_xcd = blockIdx.x >> 3;
-  const int period = (MODE == kBitmap ? 1 : 2) * P.conc;
+  const int period = (MODE == kBitmap && NWV == 4 ? 1 : 2) * P.conc;
   const int start_blk = (int)(((long long)(j_xcd % period) * u.t) / period);
   const size_t qo_base = ((size_t)u.b * s.H + u.h) * s.N + (size_t)u.t * kBlock;
   build_list<MODE, NWV>(P, u, rowid, start_blk, w, lane, reinterpret_cast<uint64_t*>(s_tile),
@@ -464,6 +466,17 @@ hipError_t launch_w(AttnParams P, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// Waves of a CU that the LDS of the units leaves resident (at most what the
+// registers do): static part of the kernel (half tiles, (max, sum) pairs, query
+// tiles, two counters) and the list, in granules of 1280 bytes out of 160 KiB.
+template <int D, int NWV>
+int lds_waves(const AttnParams& P) {
+  constexpr size_t fixed = NWV * (2 * Half<D>::kBytes + kBlock * sizeof(float2)) + (D == 128 ? 16 * Half<D>::kRow : 0) + 8;
+  const size_t granules = (fixed + list_bytes(P) + 1279) / 1280;
+  const int units = (int)(163840 / 1280 / granules);
+  return units * NWV < 4 * kWaves<D> ? units * NWV : 4 * kWaves<D>;
+}
+
 // Waves per unit.  Two fill the chip with the most units at once (d 128: 1024
 // on 256 CUs, d 64: 1536); four halve a unit's serial chain at half as many,
 // for a second merge round and the query rows read by two more waves.  So four
@@ -475,21 +488,32 @@ hipError_t launch_w(AttnParams P, hipStream_t stream) {
 //          3584 units of 25             187 / 198     3568 units of 50     362 / 341
 //   d 64    448 units of 10            28.3 / 18.7    4368 units of 5     42.1 / 57.8
 //          4048 units of 28             178 / 161    65536 units of 70    5690 / 5840
-// Bitmaps list hundreds of blocks, and their list takes LDS per unit: 8/2 heads
-// at 128K 32.8 / 29.8 ms, 28/4 heads at 32K 7.58 / 7.51 ms, always four.
 // The choice depends on the problem alone, so ugbs_attend and
 // ugbs_attend_select take the same kernel and agree bit for bit.
-template <int D>
+//
+// Bitmaps don't say how many blocks they hold, and their list is as long as the
+// sequence.  Four waves where the LDS leaves two-wave units short (at d 128 above
+// 1532 blocks: 1600 blocks, 16/4 heads, 37.2 / 34.6 ms).  Else two from about
+// where the units outnumber what is resident, as for lists; later at d 64, and
+// for the short sequences at d 128 whose unions hold most of what is visible.
+// Unions of per-row selections, two / four waves (us):
+//   d 128   2048 units, 64 blocks (k 4)       127 / 120     3200, 100 (k 4)     222 / 221
+//           2400 units, 300 blocks (k 16)     693 / 733    14336, 512 (k 32)   5620 / 6090
+//   d 64    6400 units, 200 blocks (k 16)     658 / 612     8400, 300 (k 16)   1343 / 1345
+//          14336 units, 512 blocks (k 32)    3940 / 4050
+// and with random bitmaps of few blocks, d 128: 3200 units of 3, 54 / 81.
+template <int D, int MODE>
 bool four_waves(const AttnParams& P) {
   const int n_units = P.s.B * P.s.H * P.s.T;
+  if (lds_waves<D, 4>(P) > lds_waves<D, 2>(P)) return true;
+  if (MODE == kBitmap) return n_units <= (D == 64 ? 7680 : P.s.NB < 96 ? 2560 : 1024);
   if (n_units <= (D == 64 ? 768 : 512)) return true;
   return n_units <= 6144 && n_units <= (D == 64 ? 200.0 : 160.0) * (P.expected - 4.0);
 }
 
 template <int D, int MODE>
 hipError_t launch_d(const AttnParams& P, hipStream_t stream) {
-  if (MODE == kBitmap || four_waves<D>(P)) return launch_w<D, MODE, 4>(P, stream);
-  if constexpr (MODE != kBitmap) return launch_w<D, MODE, 2>(P, stream);
+  return four_waves<D, MODE>(P) ? launch_w<D, MODE, 4>(P, stream) : launch_w<D, MODE, 2>(P, stream);
 }
 
 }  // namespace

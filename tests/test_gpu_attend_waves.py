@@ -1,8 +1,9 @@
 """Attention with the keys of a unit split over two or four waves (d 64, 128).
 
-Four waves take over when the units are few (d 128: 512 and fewer, d 64: 768),
-when there are a few rounds of units that visit many blocks, and for bitmaps;
-the parametrised shapes lie on both sides of those lines.  The lists are where the split can go wrong: single blocks (waves
+Four waves take over when the units are few (d 128: 512 and fewer, d 64: 768)
+and when there are a few rounds of units that visit many blocks; for bitmaps up
+to 1024 units of 96 and more blocks (d 64: 7680).  The parametrised shapes lie on
+both sides of those lines.  The lists are where the split can go wrong: single blocks (waves
 without an entry), the diagonal alone (a wave whose keys are all masked for
 half of the rows), rows without the diagonal, odd and even counts, empty
 rows (O = 0), widths past one 64-entry read.  A large logit scale makes the
@@ -81,7 +82,7 @@ def test_selection_in_the_kernel_gives_the_lists_bits(d, H, Hkv, T, k):
 @pytest.mark.parametrize("d", [64, 128])
 def test_bitmaps_on_both_sides_of_the_line(d):
     torch = pytest.importorskip("torch")
-    for H, Hkv, T in ((2, 1, 33), (28, 4, 150)):
+    for H, Hkv, T in ((2, 1, 33), (28, 4, 150 if d == 128 else 280)):     # four waves, two waves
         g = np.random.default_rng(4300 + d + T)
         Q, K, V = inputs(g, 1, H, Hkv, 64 * T, d)
         kv = lists(g, 1, H, T, 9)

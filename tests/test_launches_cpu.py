@@ -56,3 +56,14 @@ def test_lists_and_selection_take_the_same_kernel():
         assert form(x) == form(y), p
         assert (x["block"], x["grid"], x["dynamic"]) == (y["block"], y["grid"], y["dynamic"]), p
         assert static_lds()[x["kernel"]] == static_lds()[y["kernel"]], p
+
+
+def test_bitmaps_take_two_waves_where_units_are_many():
+    def waves(B, H, Hkv, NB, d):
+        x = launches([("attend_bitmap", make(B, H, Hkv, 64 * NB, d, 16, 0.1))])[0][1][0]
+        return x["block"] // 64
+    assert waves(1, 32, 8, 100, 128) == waves(1, 28, 4, 512, 128) == waves(1, 28, 4, 512, 64) == 2
+    assert waves(1, 8, 2, 128, 128) == waves(1, 32, 8, 80, 128) == waves(1, 32, 8, 200, 64) == 4
+    for NB in (1532, 1533):          # the list of a two-wave unit reaches a quarter of a CU's LDS
+        assert waves(1, 32, 8, NB, 128) == (2 if NB == 1532 else 4)
+    assert all(waves(1, 32, 8, NB, 64) == 2 for NB in (512, 4096))
