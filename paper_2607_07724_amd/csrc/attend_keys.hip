@@ -86,6 +86,12 @@ __device__ __forceinline__ uint32_t here(uint32_t x) {
   return x;
 }
 
+// The running maximum of a row before its first finite score.  A number, not
+// -inf: a wave may see only scores of -inf for a row (keys after the row, or
+// products that overflow) where another wave has the row's finite ones, and
+// -inf - -inf would make its part NaN; so its probabilities are 0.
+constexpr float kNoMax = -3.402823466e38f;
+
 // Waves per SIMD: what the registers allow (O alone takes D of them).
 template <int D>
 constexpr int kWaves = D == 64 ? 3 : 2;
@@ -222,7 +228,7 @@ attend_keys_kernel(AttnParams P) {
   for (int rt = 0; rt < 4; ++rt) {
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) acc_o[dt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    m_run[rt] = -__builtin_huge_valf();
+    m_run[rt] = kNoMax;
     l_run[rt] = 0.f;
   }
 
@@ -318,8 +324,6 @@ attend_keys_kernel(AttnParams P) {
     const uint32_t ko = here(koff);
 #pragma unroll
     for (int rt = 0; rt < 4; ++rt) {
-      // a row of the diagonal block may see no key of this half: reference 0 then
-      const float ref = (MASK && m_run[rt] == -__builtin_huge_valf()) ? 0.f : m_run[rt];
       // the next K half tile's loads, four at a time (see the top of the file)
       if (4 * rt < L::kLoads) {
         __builtin_amdgcn_sched_barrier(0);
@@ -332,7 +336,7 @@ attend_keys_kernel(AttnParams P) {
       float p[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i >> 2][rt][i & 3], P.scale_log2, -ref));
+        p[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i >> 2][rt][i & 3], P.scale_log2, -m_run[rt]));
         l_run[rt] += p[i];
       }
 #pragma unroll
@@ -391,7 +395,7 @@ attend_keys_kernel(AttnParams P) {
 #pragma unroll
   for (int rt = 0; rt < 4; ++rt) {
     float2 ml[NWV];
-    float M = -__builtin_huge_valf();
+    float M = kNoMax;
 #pragma unroll
     for (int v = 0; v < NWV; ++v) {
       ml[v] = s_ml[v][16 * rt + c16];
@@ -399,10 +403,9 @@ attend_keys_kernel(AttnParams P) {
     }
     float l = 0.f;
 #pragma unroll
-    for (int v = 0; v < NWV; ++v)
-      l += ml[v].x == -__builtin_huge_valf() ? 0.f : ml[v].y * __builtin_amdgcn_exp2f(ml[v].x - M);
-    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
-    const float f = m_run[rt] == -__builtin_huge_valf() ? 0.f : __builtin_amdgcn_exp2f(m_run[rt] - M) * inv;
+    for (int v = 0; v < NWV; ++v) l += ml[v].y * __builtin_amdgcn_exp2f(ml[v].x - M);
+    // (l is 0 for a row whose every score is -inf: NaN, as its softmax is)
+    const float f = __builtin_amdgcn_exp2f(m_run[rt] - M) * (l != 0.f ? 1.0f / l : __builtin_nanf(""));
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll

@@ -79,6 +79,39 @@ def test_selection_in_the_kernel_gives_the_lists_bits(d, H, Hkv, T, k):
     assert np.array_equal(host_bits(O1), host_bits(O2))
 
 
+@pytest.mark.parametrize("d,H,Hkv,T,W", [(64, 4, 2, 9, 4), (64, 32, 8, 129, 7), (128, 4, 2, 9, 4), (128, 16, 4, 129, 7)])
+def test_scores_that_overflow(d, H, Hkv, T, W):
+    """Positive queries against keys of -3e38 or 3e38: scores of -inf, whose
+    weight is 0 beside any finite score, or +inf, which makes the row NaN.
+    Every second half block is -inf, so one wave of each pair sees nothing else,
+    every third block is -inf whole, and one block is +inf."""
+    torch = pytest.importorskip("torch")
+    g = np.random.default_rng(4400 + d + T)
+    Q, K, V = (synth.bf16_bits(np.abs(g.standard_normal((1, h, 64 * T, d), dtype=np.float32))) for h in (H, Hkv, Hkv))
+    low, high = synth.bf16_bits(np.array([-3e38, 3e38], np.float32))
+    kb = K.reshape(1, Hkv, T, 64, d)
+    kb[:, :, :, 32:] = low
+    kb[:, :, 2::3] = low
+    kv = lists(g, 1, H, T, W)
+    kv[..., 0] = 0                                     # a block with finite scores in every row
+    kv[..., 1:][kv[..., 1:] == 0] = T
+    p = ugbs.Problem.make(1, H, Hkv, 64 * T, d, 3, 0.0)
+
+    def run():
+        O = torch.empty((1, H, 64 * T, d), dtype=torch.bfloat16, device="cuda")
+        ugbs.ugbs_attend(p, dev_bf16(Q), dev_bf16(K), dev_bf16(V), dev(kv), O)
+        torch.cuda.synchronize()
+        return host_bits(O)
+    O = run()
+    mx, rms = attention_error(O, oracle.attend(Q, K, V, kv_idx=kv))
+    assert mx <= ATOL_MAX and rms <= ATOL_RMS
+    kb[:, :, 4, 63] = high                             # the last key of block 4
+    hit = np.repeat((kv == 4).any(-1), 64, axis=-1)
+    hit.reshape(1, H, T, 64)[:, :, 4, :63] = False     # rows before it don't see it
+    O2 = run()
+    assert np.isnan(bf16_to_f64(O2)[hit]).all() and np.array_equal(O2[~hit], O[~hit])
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_bitmaps_on_both_sides_of_the_line(d):
     torch = pytest.importorskip("torch")
