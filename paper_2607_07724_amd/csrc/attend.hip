@@ -162,7 +162,7 @@ attend_kernel(AttnParams P) {
   float m_run[RT], l_run[RT];
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
-    m_run[rt] = -__builtin_huge_valf();
+    m_run[rt] = kNoMax;
     l_run[rt] = 0.f;
   }
 
@@ -362,7 +362,8 @@ attend_kernel(AttnParams P) {
     float l = l_run[rt];
     l += __shfl_xor(l, 16);
     l += __shfl_xor(l, 32);
-    const float inv = (l > 0.f) ? 1.0f / l : 0.f;
+    // (l is 0 for a row whose every score is -inf: NaN, as its softmax is)
+    const float inv = l != 0.f ? 1.0f / l : __builtin_nanf("");
     const int r = RPW * w + 16 * rt + c16;
     uint16_t* orow = P.O + (qo_base + r) * D;
 #pragma unroll

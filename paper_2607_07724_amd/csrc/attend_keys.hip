@@ -86,12 +86,6 @@ __device__ __forceinline__ uint32_t here(uint32_t x) {
   return x;
 }
 
-// The running maximum of a row before its first finite score.  A number, not
-// -inf: a wave may see only scores of -inf for a row (keys after the row, or
-// products that overflow) where another wave has the row's finite ones, and
-// -inf - -inf would make its part NaN; so its probabilities are 0.
-constexpr float kNoMax = -3.402823466e38f;
-
 // Waves per SIMD: what the registers allow (O alone takes D of them).
 template <int D>
 constexpr int kWaves = D == 64 ? 3 : 2;

@@ -60,6 +60,12 @@ hipError_t launch_attend_keys(const AttnParams& P, int mode, hipStream_t stream)
 
 namespace {
 
+// The running maximum of a row before its first finite score.  A number, not
+// -inf: the first keys a wave sees may all have scores of -inf for a row (keys
+// after the row, or products that overflow) where later ones, or another wave's,
+// are finite, and -inf - -inf would make the row NaN; so their probabilities are 0.
+constexpr float kNoMax = -3.402823466e38f;
+
 // Where a tile's blocks come from.  kSelectWide: kSelect for rows of more
 // than 2048 candidate blocks (64 instead of 32 candidates per lane).
 enum Mode { kLists = 0, kSelect = 1, kBitmap = 2, kSelectWide = 3 };

@@ -47,8 +47,8 @@ def inputs(g, B, H, Hkv, N, d):
 
 
 @pytest.mark.parametrize("scale", [0.0, 0.9])
-@pytest.mark.parametrize("d,B,H,Hkv,T,W", [(64, 1, 4, 2, 9, 4), (64, 1, 3, 3, 70, 67), (64, 1, 32, 8, 129, 7),
-                                           (128, 1, 4, 2, 9, 4), (128, 2, 2, 1, 70, 67), (128, 1, 16, 4, 129, 7)])
+@pytest.mark.parametrize("d,B,H,Hkv,T,W", [(64, 1, 4, 2, 9, 4), (64, 1, 4, 2, 9, 8), (64, 1, 3, 3, 70, 67), (64, 1, 32, 8, 129, 7),
+                                           (128, 1, 4, 2, 9, 4), (128, 1, 4, 2, 9, 8), (128, 2, 2, 1, 70, 67), (128, 1, 16, 4, 129, 7)])
 def test_lists_of_every_kind(d, B, H, Hkv, T, W, scale):
     torch = pytest.importorskip("torch")
     g = np.random.default_rng(4100 + d + T + W)
@@ -79,7 +79,8 @@ def test_selection_in_the_kernel_gives_the_lists_bits(d, H, Hkv, T, k):
     assert np.array_equal(host_bits(O1), host_bits(O2))
 
 
-@pytest.mark.parametrize("d,H,Hkv,T,W", [(64, 4, 2, 9, 4), (64, 32, 8, 129, 7), (128, 4, 2, 9, 4), (128, 16, 4, 129, 7)])
+@pytest.mark.parametrize("d,H,Hkv,T,W", [(64, 4, 2, 9, 4), (64, 4, 2, 9, 8), (64, 32, 8, 129, 7), (128, 4, 2, 9, 4),
+                                           (128, 4, 2, 9, 8), (128, 16, 4, 129, 7), (256, 4, 2, 9, 8)])
 def test_scores_that_overflow(d, H, Hkv, T, W):
     """Positive queries against keys of -3e38 or 3e38: scores of -inf, whose
     weight is 0 beside any finite score, or +inf, which makes the row NaN.
