@@ -379,7 +379,8 @@ template <int D, int MODE>
 hipError_t launch_t(AttnParams P, hipStream_t stream) {
   const size_t smem = list_bytes(P);
   constexpr auto kernel = attend_kernel<D, MODE>;
-  P.conc = xcd_concurrency<kernel, (D > 128)>(Geo<D>::kThreads, smem);
+  const hipError_t e = xcd_concurrency<kernel, (D > 128)>(Geo<D>::kThreads, smem, &P.conc);
+  if (e != hipSuccess) return e;
   kernel<<<P.order.grid, Geo<D>::kThreads, smem, stream>>>(P);
   return hipGetLastError();
 }

@@ -458,7 +458,8 @@ template <int D, int MODE, int NWV>
 hipError_t launch_w(AttnParams P, hipStream_t stream) {
   const size_t smem = list_bytes(P);
   constexpr auto kernel = attend_keys_kernel<D, MODE, NWV>;
-  P.conc = xcd_concurrency<kernel, NWV * 2 * Half<D>::kBytes >= 65536>(64 * NWV, smem);
+  const hipError_t e = xcd_concurrency<kernel, NWV * 2 * Half<D>::kBytes >= 65536>(64 * NWV, smem, &P.conc);
+  if (e != hipSuccess) return e;
   kernel<<<P.order.grid, 64 * NWV, smem, stream>>>(P);
   return hipGetLastError();
 }

@@ -363,23 +363,28 @@ inline size_t list_bytes(const AttnParams& P) {
 // raised first (to the widest list, the same value whoever calls).
 constexpr int kMaxDevices = 64;
 template <auto KERNEL, bool RAISE = false>
-int xcd_concurrency(int threads, size_t smem) {
+hipError_t xcd_concurrency(int threads, size_t smem, int* conc) {
   static std::atomic<uint64_t> cache[kMaxDevices];
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev >= kMaxDevices) dev = -1;
   if (dev >= 0) {
     const uint64_t e = cache[dev].load(std::memory_order_relaxed);
-    if (e != 0 && (e >> 32) == (uint64_t)smem) return (int)(uint32_t)e;
+    if (e != 0 && (e >> 32) == (uint64_t)smem) {
+      *conc = (int)(uint32_t)e;
+      return hipSuccess;
+    }
   }
-  if (RAISE)
-    (void)hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)sizeof(uint16_t) * UGBS_MAX_KV_WIDTH);
+  if (RAISE) {
+    const hipError_t e = hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)sizeof(uint16_t) * UGBS_MAX_KV_WIDTH);
+    if (e != hipSuccess) return e;
+  }
   int per_cu = 0, n_cu = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERNEL, threads, smem) != hipSuccess) per_cu = 1;
   if (dev < 0 || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n_cu = 8;
-  const int conc = per_cu * n_cu / 8 > 0 ? per_cu * n_cu / 8 : 1;
-  if (dev >= 0) cache[dev].store(((uint64_t)smem << 32) | (uint32_t)conc, std::memory_order_relaxed);
-  return conc;
+  *conc = per_cu * n_cu / 8 > 0 ? per_cu * n_cu / 8 : 1;
+  if (dev >= 0) cache[dev].store(((uint64_t)smem << 32) | (uint32_t)*conc, std::memory_order_relaxed);
+  return hipSuccess;
 }
 
 }  // namespace

@@ -67,3 +67,13 @@ def test_bitmaps_take_two_waves_where_units_are_many():
     for NB in (1532, 1533):          # the list of a two-wave unit reaches a quarter of a CU's LDS
         assert waves(1, 32, 8, NB, 128) == (2 if NB == 1532 else 4)
     assert all(waves(1, 32, 8, NB, 64) == 2 for NB in (512, 4096))
+
+
+def test_a_refused_lds_limit_is_reported():
+    """Kernels with 64 KiB of static LDS need their dynamic limit raised; the
+    call fails, without a launch, where the runtime refuses that."""
+    p256, p128 = make(1, 4, 1, 64 * 300, 256, 16, 0.1), make(1, 4, 1, 64 * 100, 128, 16, 0.1)
+    calls = [(fn, p, p.W if fn == "attend" else 0, True) for p in (p256, p128)
+             for fn in ("attend", "attend_select", "attend_bitmap")]
+    for st, xs in launches(calls):
+        assert (st, xs) == (8, [])
