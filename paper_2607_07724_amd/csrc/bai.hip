@@ -608,7 +608,10 @@ hipError_t launch_bai_tiles(const Shape& s, const float* scores, const float* ta
   while (n2 < r1 && n2 < s.NB) n2 <<= 1;
   const int sel = 8 * n2 > 4 * (s.NB + 8) ? 8 * n2 : 4 * (s.NB + 8);
   P.sel_bytes = (sel + 15) & ~15;
-  P.top_bytes = 8 * ((s.W + 7) & ~7);   // values and positions, each padded to 8 ranks
+  // values and positions of the top R', each padded to 8 ranks; a tile that uses
+  // them has R' + 1 <= |C(t)| <= N_B - 2 as well, so wider budgets take no more
+  const int ranks = s.W < s.NB ? s.W : s.NB;
+  P.top_bytes = 8 * ((ranks + 7) & ~7);
   const size_t smem = (size_t)kBaiUnits * (P.sel_bytes + P.top_bytes);
   // the kernel for the shortest row that holds N_B: phase 1 runs through all of
   // its slots' code (200 blocks, 28 heads: 74 -> 48 us with this and the rest above)

@@ -77,3 +77,13 @@ def test_a_refused_lds_limit_is_reported():
              for fn in ("attend", "attend_select", "attend_bitmap")]
     for st, xs in launches(calls):
         assert (st, xs) == (8, [])
+
+
+def test_diagnostics_of_wide_budgets_fit_the_lds():
+    """Budgets beyond a row's candidates give records that are not valid; the
+    launch still has to fit a workgroup's LDS, whatever k and rho."""
+    probs = [make(1, 4, 1, 64 * NB, 64, k, 0.1, rho=rho)
+             for NB in (40, 512, 1025, 2048) for k, rho in ((4, 2), (766, 4), (767, 4), (3066, 1), (1533, 2), (4096, 1), (512, 8))]
+    for p, (st, xs) in zip(probs, launches([("bai_tiles", p, 16) for p in probs])):
+        assert st == 0 and len(xs) == 1
+        assert static_lds()[xs[0]["kernel"]] + xs[0]["dynamic"] <= 160 * 1024, p
