@@ -1,9 +1,10 @@
 """The route at the edges of its search and of its row copy, bit for bit.
 
-Tile counts around a wave's 64 keys, the workgroup's 1024 threads and the
-largest accepted; sigmas with heavy ties (the quantile search ends early only
-on distinct ones), all equal, and zero; rows of four-slot accesses and not,
-lists whose pointers are not 16-byte aligned, in place and out of place.
+Tile counts around a wave's 64 keys, the 1024 up to which one wave searches
+(and the workgroup's threads), twice that, and the largest accepted; sigmas
+with heavy ties (the quantile search ends early only on distinct ones), all
+equal, and zero; rows of four-slot accesses and not, lists whose pointers are
+not 16-byte aligned, in place and out of place.
 """
 import numpy as np
 import pytest
@@ -17,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T,k,rho", [(1, 3, 2), (5, 3, 1), (63, 4, 2), (64, 5, 2), (65, 4, 3), (66, 33, 2), (513, 64, 2),
-                                     (1024, 6, 4), (1025, 5, 3), (4096, 4, 2)])
+                                     (1024, 6, 4), (1025, 5, 3), (2048, 9, 2), (2049, 33, 2), (4096, 4, 2)])
 @pytest.mark.parametrize("kind", ["distinct", "ties", "equal"])
 def test_route_rows(T, k, rho, kind):
     torch = pytest.importorskip("torch")
