@@ -458,6 +458,12 @@ __global__ void __launch_bounds__(64 * kMaxGroup) score_kernel(SelParams P) {
 // one column tile's operands fit without spilling.  Measured at 128K:
 // score + select 1.50 -> 1.36 ms (P7 1.28 -> 1.18, C3 0.45 -> 0.41),
 // outputs bit-identical.
+template <int OUT>
+__global__ void __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(3, 3)))
+score_kernel_q128(SelParams P) {
+  score_body<128, true, OUT>(P);
+}
+
 // The same with two units per wave (249 registers, two waves per SIMD): each
 // metadata operand read from the LDS, and each chunk fetched into it, serves
 // twice the matrix instructions; the LDS reads and the staging were as long as
@@ -466,12 +472,6 @@ template <int OUT>
 __global__ void __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(2, 2)))
 score_kernel_q128x2(SelParams P) {
   score_body<128, true, OUT, 2>(P);
-}
-
-template <int OUT>
-__global__ void __launch_bounds__(64 * kMaxGroup) __attribute__((amdgpu_waves_per_eu(3, 3)))
-score_kernel_q128(SelParams P) {
-  score_body<128, true, OUT>(P);
 }
 
 // K-mean d 128 tile scores: the body held to 96 registers, five waves per
@@ -487,9 +487,10 @@ score_kernel_k128(SelParams P) {
 
 // One wave per (b, h, t) unit, heaviest tile first; reads the unit's
 // candidate scores (packed rows of the score kernel, or a full [.., N_B] row)
-// SLOTS: candidates per lane held in registers (N_B / 64 rounded up to 32 or
-// 64: rows of up to 2048 or 4096 blocks).
-template <bool PACKED, int SLOTS>
+// SLOTS: candidates per lane held in registers (N_B / 64 rounded up to one of
+// five sizes).  WIDE: more than 192 candidates wanted, which the pre-filter
+// doesn't serve: compiled without it.
+template <bool PACKED, int SLOTS, bool WIDE>
 __global__ void __launch_bounds__(64 * kSelWaves) select_kernel(SelParams P) {
   extern __shared__ __align__(16) unsigned char smem[];
   const Shape& s = P.s;
@@ -539,31 +540,48 @@ __global__ void __launch_bounds__(64 * kSelWaves) select_kernel(SelParams P) {
   constexpr int kGroup = SLOTS < 8 ? SLOTS : 8;
   const int nslots = (nc + 63) / 64;
   uint32_t keys[kMaxSlots];
+  if constexpr (WIDE) {
+    // slot by slot: this form leaves the threshold search over all slots the
+    // faster code (194..256 wanted of 2048 blocks, 4 heads, d 256: the selection
+    // 55 -> 35 us, 3% and more below the grouped form at 1200-2048 blocks)
+    float raw[kMaxSlots];
 #pragma unroll
-  for (int s0 = 0; s0 < kMaxSlots; s0 += kGroup) {
-    if (s0 < nslots) {
-      // the group's loads first (clamped in-row addresses), then the
-      // conversions, so the loads are in flight together
-      float raw[kGroup];
+    for (int sl = 0; sl < kMaxSlots; ++sl) {
+      const int p = 64 * sl + lane;
+      raw[sl] = (sl < nslots) ? src[p < nc ? p : nc - 1] : 0.f;
+    }
 #pragma unroll
-      for (int j = 0; j < kGroup; ++j) {
-        const int p = 64 * (s0 + j) + lane;
-        raw[j] = src[p < nc ? p : nc - 1];
+    for (int sl = 0; sl < kMaxSlots; ++sl) {
+      const int p = 64 * sl + lane;
+      keys[sl] = (sl < nslots && p < nc) ? order_key(raw[sl]) : 0u;  // valid keys are >= 0x007fffff
+    }
+  } else {
+#pragma unroll
+    for (int s0 = 0; s0 < kMaxSlots; s0 += kGroup) {
+      if (s0 < nslots) {
+        // the group's loads first (clamped in-row addresses), then the
+        // conversions, so the loads are in flight together
+        float raw[kGroup];
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) {
+          const int p = 64 * (s0 + j) + lane;
+          raw[j] = src[p < nc ? p : nc - 1];
+        }
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j)
+          keys[s0 + j] = (64 * (s0 + j) + lane < nc) ? order_key(raw[j]) : 0u;
+      } else {
+#pragma unroll
+        for (int j = 0; j < kGroup; ++j) keys[s0 + j] = 0u;
       }
-#pragma unroll
-      for (int j = 0; j < kGroup; ++j)
-        keys[s0 + j] = (64 * (s0 + j) + lane < nc) ? order_key(raw[j]) : 0u;  // valid keys are >= 0x007fffff
-    } else {
-#pragma unroll
-      for (int j = 0; j < kGroup; ++j) keys[s0 + j] = 0u;
     }
   }
   bool filtered = false, sort_all = false;
-  const bool whole = nc <= 128 && R <= 128;
+  const bool whole = !WIDE && nc <= 128 && R <= 128;
   if (whole) {
     sort_all = true;
     filtered = true;
-  } else if (R <= 192 && nc > R) {
+  } else if (!WIDE && R <= 192 && nc > R) {
     // (slots past the row hold key 0, the smallest: no guard needed within a
     // group here or in the compaction below, where only keys >= t0 > 0 are
     // taken)
@@ -755,19 +773,26 @@ hipError_t launch_score(SelParams P, hipStream_t stream) {
   return hipGetLastError();
 }
 
-template <bool PACKED, int SLOTS>
-hipError_t launch_select_s(const SelParams& P, hipStream_t stream) {
+template <bool PACKED, int SLOTS, bool WIDE>
+hipError_t launch_select_w(const SelParams& P, hipStream_t stream) {
   const size_t smem = (size_t)kSelWaves * P.wave_lds;
   if (smem > 65536) {  // large budgets (k near N_B): raise the dynamic-LDS limit
-    const hipError_t e = hipFuncSetAttribute((const void*)select_kernel<PACKED, SLOTS>,
+    const hipError_t e = hipFuncSetAttribute((const void*)select_kernel<PACKED, SLOTS, WIDE>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
   }
   const int n_units = P.s.B * P.s.H * P.s.T;
   const int n_wg = (n_units + kSelWaves - 1) / kSelWaves;
   const int grid = ((n_wg + 7) / 8) * 8;
-  select_kernel<PACKED, SLOTS><<<grid, 64 * kSelWaves, smem, stream>>>(P);
+  select_kernel<PACKED, SLOTS, WIDE><<<grid, 64 * kSelWaves, smem, stream>>>(P);
   return hipGetLastError();
+}
+
+template <bool PACKED, int SLOTS>
+hipError_t launch_select_s(const SelParams& P, hipStream_t stream) {
+  // candidates of a long row that are wanted (see R in the kernel)
+  const int wanted = P.idx_sorted && P.s.W - 2 > P.s.k - 1 ? P.s.W - 2 : P.s.k - 1;
+  return wanted > 192 ? launch_select_w<PACKED, SLOTS, true>(P, stream) : launch_select_w<PACKED, SLOTS, false>(P, stream);
 }
 
 template <bool PACKED>

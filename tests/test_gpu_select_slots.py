@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("T", [3, 64, 66, 130, 131, 256, 257, 512, 513, 1024, 1025, 2049])
-@pytest.mark.parametrize("k,rho", [(3, 1), (5, 2), (65, 2), (66, 2), (129, 1), (130, 2)])
+@pytest.mark.parametrize("k,rho", [(3, 1), (5, 2), (65, 2), (66, 2), (129, 1), (97, 2), (98, 2), (194, 1), (130, 2)])
 def test_row_sizes(T, k, rho):
     torch = pytest.importorskip("torch")
     g = np.random.default_rng(5000 + T + k)
