@@ -406,14 +406,27 @@ hipError_t launch_t(AttnParams P, hipStream_t stream) {
 // The choice depends on the problem and the list's width alone, so ugbs_attend
 // and ugbs_attend_select take the same kernel and agree bit for bit.
 inline bool coupled_walk(const AttnParams& P) {
-  return P.s.d == 128 && P.s.NB >= 1408 && (P.s.backbone == UGBS_KMEAN || P.expected * P.s.NB >= 300000.0);
+  return P.s.NB >= 1408 && (P.s.backbone == UGBS_KMEAN || P.expected * P.s.NB >= 300000.0);
+}
+
+// d 64 and 128 lists of three or four blocks where the units are few: the merge of
+// attend_keys.hip's waves is longer than the half blocks they save.  Measured (us,
+// here / two / four waves there):
+//   d 128   64 units of 3 blocks    9.1 / 9.7 / 10.9    512 of 3    12.2 / 13.3 / 15.5
+//           64 of 4.2, 6 at most   12.8 / 13.1 / 12.2  1024 of 3    17.4 / 17.9 / 27.8
+//   d 64    64 of 3                 7.1 / 7.2 / 7.9     512 of 3     8.9 / 9.6 / 10.7
+//           1024 of 3              10.8 / 11.4 / 17.6  1120 of 3    15.8 / 13.2 / 18.8
+inline bool few_short_lists(const AttnParams& P) {
+  return P.longest <= 4.0 && P.s.B * P.s.H * P.s.T <= 1024;
 }
 
 template <int MODE>
 hipError_t launch_mode(const AttnParams& P, hipStream_t stream) {
   if (P.s.d == 256) return launch_t<256, MODE>(P, stream);
   if constexpr (MODE != kBitmap)
-    if (coupled_walk(P)) return launch_t<128, MODE>(P, stream);
+    if (P.s.d == 128 && (coupled_walk(P) || few_short_lists(P))) return launch_t<128, MODE>(P, stream);
+  if constexpr (MODE == kLists || MODE == kSelect)
+    if (P.s.d == 64 && few_short_lists(P)) return launch_t<64, MODE>(P, stream);
   return launch_attend_keys(P, MODE, stream);
 }
 
@@ -432,6 +445,7 @@ hipError_t launch_attend(const Shape& s, const uint16_t* Q, const uint16_t* K,
   P.O = O;
   P.kv_width = kv_width;
   P.expected = expected_blocks(s, kv_width);
+  P.longest = longest_list(s, kv_width);
   P.scale_log2 = s.scale * 1.4426950408889634f;
   return launch_mode<kLists>(P, stream);
 }
@@ -449,6 +463,7 @@ hipError_t launch_attend_select(const Shape& s, const uint16_t* Q, const uint16_
   // at most |F| + (rho k - |F|) distinct blocks per tile, and never more than t + 1
   P.kv_width = s.W < s.NB ? s.W : s.NB;
   P.expected = expected_blocks(s, s.W);
+  P.longest = longest_list(s, s.W);
   P.scale_log2 = s.scale * 1.4426950408889634f;
   const unsigned char* ws = static_cast<const unsigned char*>(workspace);
   P.sel_scores = scores;
@@ -468,7 +483,7 @@ hipError_t launch_attend_bitmap(const Shape& s, const uint16_t* Q, const uint16_
   P.V = V;
   P.O = O;
   P.kv_width = s.NB;  // a row may list every visible block
-  P.expected = s.NB;
+  P.expected = P.longest = s.NB;
   P.scale_log2 = s.scale * 1.4426950408889634f;
   P.bitmap = bitmap;
   P.nw = (s.NB + 31) / 32;

@@ -480,12 +480,23 @@ int lds_waves(const AttnParams& P) {
 // for a second merge round and the query rows read by two more waves.  So four
 // where they still hold every unit at once, and, up to a few rounds of units,
 // where a unit visits enough blocks to pay for the longer ends; the expected
-// blocks come from the budget.  Measured with two / four waves (us):
-//   d 128   256 units of 16 blocks     39.1 / 26.3     928 units of 7      24.6 / 32.3
-//           912 units of 26            89.2 / 71.8    2048 units of 35     188 / 162
-//          3584 units of 25             187 / 198     3568 units of 50     362 / 341
-//   d 64    448 units of 10            28.3 / 18.7    4368 units of 5     42.1 / 57.8
-//          4048 units of 28             178 / 161    65536 units of 70    5690 / 5840
+// blocks come from the budget.  A short list that is as long as most others (few
+// tiles expand) leaves no long chain to halve: two there, unless they would leave
+// most of a second round empty.  Measured with two / four waves (us):
+//   d 128   256 units of 16 blocks      39.1 / 26.3     928 units of 7       24.6 / 32.3
+//           912 units of 26             89.2 / 71.8    2048 units of 35       188 / 162
+//           900 of 10 (32 at most)     60.0 / 53.0
+//          2048 of 17.6 (32)            93.9 / 96.8    2048 of 13            77.0 / 83.1
+//          1792 of 17.6 (32)            86.5 / 85.9    3584 of 25             187 / 198
+//          3568 of 46 (66)               351 / 357     5200 of 53 (96)        715 / 689
+//     no tile expands (rho 1, or few):
+//          1024 of 11 (16)              37.5 / 43.0    1024 of 24            48.4 / 52.7
+//           892 of 24                   51.0 / 59.9    2240 of 24             104 / 121
+//          1200 of 24, 600 tiles        91.2 / 82.3    1120 of 24, 40 tiles  52.4 / 60.6
+//   d 64    448 units of 10             28.3 / 18.7    4368 units of 5       42.1 / 57.8
+//          4048 units of 28              178 / 161    65536 units of 70      5690 / 5840
+//          1024 of 11 (16)              24.6 / 28.3     892 of 24             33.6 / 38.0
+//           640 of 4 (6)                13.4 / 14.4
 // The choice depends on the problem alone, so ugbs_attend and
 // ugbs_attend_select take the same kernel and agree bit for bit.
 //
@@ -505,8 +516,13 @@ bool four_waves(const AttnParams& P) {
   const int n_units = P.s.B * P.s.H * P.s.T;
   if (lds_waves<D, 4>(P) > lds_waves<D, 2>(P)) return true;
   if (MODE == kBitmap) return n_units <= (D == 64 ? 7680 : P.s.NB < 96 ? 2560 : 1024);
-  if (n_units <= (D == 64 ? 768 : 512)) return true;
-  return n_units <= 6144 && n_units <= (D == 64 ? 200.0 : 160.0) * (P.expected - 4.0);
+  if (n_units <= (D == 64 && P.longest > 6.0 ? 768 : 512)) return true;
+  const double mean = mean_blocks(P);
+  if (P.expected < 32.0 && P.longest < 1.3 * (mean + 4.0)) {
+    const bool second_round_short = n_units > 1024 && n_units <= 1536 && mean > 0.9 * P.expected;
+    if (D == 64 ? n_units <= 1152 : !second_round_short) return false;
+  }
+  return n_units <= 6144 && n_units <= (D == 64 ? 200.0 : n_units <= 1536 || P.s.G < 4 ? 160.0 : 140.0) * (P.expected - 4.0);
 }
 
 template <int D, int MODE>

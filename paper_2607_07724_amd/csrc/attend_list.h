@@ -42,6 +42,7 @@ struct AttnParams {
   uint16_t* O;
   int kv_width;
   double expected;   // kept blocks of a unit, as the budget has it
+  double longest;    // and the most a unit keeps
   AttendOrder order;
   int conc;          // units resident at once on one XCD (rotation period)
   float scale_log2;
@@ -344,6 +345,16 @@ __device__ __forceinline__ void build_list(const AttnParams& P, const Unit& u, s
 inline double expected_blocks(const Shape& s, int width) {
   const double e = width == s.W ? s.k + s.q * (s.W - s.k) : width;
   return e < s.NB ? e : s.NB;
+}
+
+inline double longest_list(const Shape& s, int width) {
+  const double m = width == s.W && s.q == 0.0 ? s.k : width;   // q 0: no tile triggers
+  return m < s.NB ? m : s.NB;
+}
+
+// Mean of the kept blocks over the tiles of a sequence: tile t sees t + 1.
+inline double mean_blocks(const AttnParams& P) {
+  return P.expected - P.expected * (P.expected - 1.0) / (2.0 * P.s.T);
 }
 
 // LDS of a unit's list: at most kv_width distinct blocks, and at most N_B, 16 bits

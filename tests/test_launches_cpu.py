@@ -46,8 +46,8 @@ def test_lists_and_selection_take_the_same_kernel():
     """The two entry points agree bit for bit, so they have to split a unit's
     work alike: same kernel, same block, same LDS for the list."""
     probs = [make(B, H, Hkv, 64 * NB, d, k, q, bb, rho=rho)
-             for B, H, Hkv in ((1, 4, 1), (1, 28, 4), (2, 8, 2)) for NB in (16, 100, 700, 1407, 1408, 2049, 4096)
-             for d in (64, 128, 256) for k, q, bb, rho in ((4, 0.25, ugbs.KMEAN, 2), (64, 0.1, ugbs.QUEST, 2),
+             for B, H, Hkv in ((1, 4, 1), (1, 28, 4), (2, 8, 2)) for NB in (4, 16, 100, 700, 1407, 1408, 2049, 4096)
+             for d in (64, 128, 256) for k, q, bb, rho in ((3, 0.0, ugbs.QUEST, 2), (4, 0.25, ugbs.KMEAN, 2), (64, 0.1, ugbs.QUEST, 2),
                                                             (400, 0.4, ugbs.QUEST, 4))]
     a = launches([("attend", p, p.W) for p in probs])
     b = launches([("attend_select", p) for p in probs])
@@ -69,6 +69,16 @@ def test_bitmaps_take_two_waves_where_units_are_many():
     assert all(waves(1, 32, 8, NB, 64) == 2 for NB in (512, 4096))
 
 
+def test_diagnostics_of_wide_budgets_fit_the_lds():
+    """Budgets beyond a row's candidates give records that are not valid; the
+    launch still has to fit a workgroup's LDS, whatever k and rho."""
+    probs = [make(1, 4, 1, 64 * NB, 64, k, 0.1, rho=rho)
+             for NB in (40, 512, 1025, 2048) for k, rho in ((4, 2), (766, 4), (767, 4), (3066, 1), (1533, 2), (4096, 1), (512, 8))]
+    for p, (st, xs) in zip(probs, launches([("bai_tiles", p, 16) for p in probs])):
+        assert st == 0 and len(xs) == 1
+        assert static_lds()[xs[0]["kernel"]] + xs[0]["dynamic"] <= 160 * 1024, p
+
+
 def test_a_refused_lds_limit_is_reported():
     """Kernels with 64 KiB of static LDS need their dynamic limit raised; the
     call fails, without a launch, where the runtime refuses that."""
@@ -79,11 +89,18 @@ def test_a_refused_lds_limit_is_reported():
         assert (st, xs) == (8, [])
 
 
-def test_diagnostics_of_wide_budgets_fit_the_lds():
-    """Budgets beyond a row's candidates give records that are not valid; the
-    launch still has to fit a workgroup's LDS, whatever k and rho."""
-    probs = [make(1, 4, 1, 64 * NB, 64, k, 0.1, rho=rho)
-             for NB in (40, 512, 1025, 2048) for k, rho in ((4, 2), (766, 4), (767, 4), (3066, 1), (1533, 2), (4096, 1), (512, 8))]
-    for p, (st, xs) in zip(probs, launches([("bai_tiles", p, 16) for p in probs])):
-        assert st == 0 and len(xs) == 1
-        assert static_lds()[xs[0]["kernel"]] + xs[0]["dynamic"] <= 160 * 1024, p
+def test_waves_per_unit_of_lists():
+    """(kernel, waves) around the lines of the choice: few short lists on the
+    coupled kernel, four waves for few units or chains that expansion makes long."""
+    def form(d, H, Hkv, NB, k, q, rho=2):
+        x = launches([("attend", make(1, H, Hkv, 64 * NB, d, k, q, rho=rho), rho * k)])[0][1][0]
+        return ("keys" if "keys" in x["kernel"] else "coupled", x["block"] // 64)
+    for d in (64, 128):
+        assert form(d, 4, 1, 16, 3, 0.4, 1) == form(d, 4, 1, 16, 3, 0.0) == form(d, 32, 8, 32, 4, 0.1, 1) == ("coupled", 2)
+        assert form(d, 4, 1, 16, 3, 0.1) == form(d, 4, 1, 16, 5, 0.0, 1) == ("keys", 4)
+        assert form(d, 32, 8, 33, 3, 0.0, 1) == ("keys", 2)
+        assert form(d, 32, 8, 32, 24, 0.1, 1) == ("keys", 2)         # no chain longer than the others
+        assert form(d, 32, 8, 32, 24, 0.1) == ("keys", 4)
+    assert form(64, 4, 1, 160, 3, 0.4) == ("keys", 2) and form(64, 4, 1, 160, 4, 0.4) == ("keys", 4)
+    assert form(128, 32, 8, 64, 16, 0.1) == ("keys", 2) and form(128, 32, 16, 64, 16, 0.1) == ("keys", 4)
+    assert form(128, 3, 3, 300, 8, 0.1, 4) == ("keys", 4)
