@@ -90,12 +90,18 @@ def flops_scores(B: int, H: int, T: int, d: int, backbone: int) -> float:
     return 2.0 * KD * B * H * 64 * cand
 
 
-ATTENTION_SOURCES = ("attend.hip", "attend_common.h", "select_common.h", "ugbs_internal.h")
+# the attention kernel (over kv_idx lists) that each workload's sizes take
+ATTENTION_KERNELS = {"C1": "attend_keys_kernel<64, 0, 4>", "C2": "attend_keys_kernel<128, 0, 2>",
+                     "C3": "attend_keys_kernel<128, 0, 2>", "C4": "attend_keys_kernel<128, 0, 2>",
+                     "C5": "attend_keys_kernel<128, 0, 2>", "C6": "attend_kernel<256, 0>",
+                     "P7": "attend_keys_kernel<128, 0, 2>", "L8": "attend_keys_kernel<128, 0, 2>"}
+ATTENTION_SOURCES = ("attend.hip", "attend_keys.hip", "attend_list.h", "attend_common.h", "select_common.h",
+                     "ugbs_internal.h")
 
 
 def attention_source_sha256():
-    """SHA-256 over the attention kernel's translation unit and the headers
-    it includes (in a fixed order), the key of the recorded traffic."""
+    """SHA-256 over the attention kernels' translation units and the headers
+    they include (in a fixed order), the key of the recorded traffic."""
     import hashlib
     h = hashlib.sha256()
     for name in ATTENTION_SOURCES:
@@ -115,7 +121,7 @@ def measured_traffic(w, q_override):
     if w.name != "C4" or q_override not in (None, 0.1) or not os.path.exists(path):
         return None
     with open(path) as f:
-        rec = json.load(f).get("attend_kernel<128>")
+        rec = json.load(f).get(ATTENTION_KERNELS[w.name])
     if rec is None or rec.get("source_sha256") != attention_source_sha256():
         return None
     return round(rec["fetch_bytes"] + rec["write_bytes"])
@@ -436,7 +442,7 @@ def main():
     kept = (kv != w.NB).sum(axis=-1)
     bytes_kv_gathered = 2.0 * float(kept.sum()) * 64 * w.d * 2
     roofline = {
-        "kernel": f"attend_kernel<{w.d}, 0> (kv_idx lists)",
+        "kernel": ("" if a.q is not None else ATTENTION_KERNELS[w.name] + " ") + "(kv_idx lists)",
         "bound": "mfma",
         "achieved": round(f_att / (att_ms * 1e-3) / 1e12, 2),
         "peak": PEAK_BF16_TFLOPS,

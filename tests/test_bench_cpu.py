@@ -2,6 +2,7 @@
 staleness rule of the recorded HBM traffic, and the one-GPU contract."""
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -10,6 +11,7 @@ import numpy as np
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 import bench  # noqa: E402
+import paper_2607_07724_amd as ugbs  # noqa: E402
 from paper_2607_07724_amd import synth  # noqa: E402
 
 
@@ -54,22 +56,43 @@ def test_traffic_record_is_used_only_for_the_source_it_was_taken_on(tmp_path, mo
     (tmp_path / "profiles").mkdir()
     src_dir = tmp_path / "paper_2607_07724_amd" / "csrc"
     src_dir.mkdir(parents=True)
-    (src_dir / "attend.hip").write_bytes(b"kernel source A")
-    (src_dir / "attend_common.h").write_bytes(b"helpers A")
+    for name in bench.ATTENTION_SOURCES:
+        (src_dir / name).write_bytes(b"A of " + name.encode())
     monkeypatch.setattr(bench, "ROOT", str(tmp_path))
     sha = bench.attention_source_sha256()
-    rec = {"attend_kernel<128>": {"source_sha256": sha, "fetch_bytes": 100.4, "write_bytes": 20.2}}
+    rec = {bench.ATTENTION_KERNELS["C4"]: {"source_sha256": sha, "fetch_bytes": 100.4, "write_bytes": 20.2}}
     (tmp_path / "profiles" / "traffic.json").write_text(json.dumps(rec))
     c4 = synth.WORKLOADS["C4"]
     assert bench.measured_traffic(c4, None) == 121
     assert bench.measured_traffic(c4, 0.25) is None               # another workload
     assert bench.measured_traffic(synth.WORKLOADS["C2"], None) is None
-    (src_dir / "attend_common.h").write_bytes(b"helpers B")      # an included header changed since
-    assert bench.measured_traffic(c4, None) is None
-    (src_dir / "attend_common.h").write_bytes(b"helpers A")
-    assert bench.measured_traffic(c4, None) == 121
-    (src_dir / "attend.hip").write_bytes(b"kernel source B")      # kernel changed since
-    assert bench.measured_traffic(c4, None) is None
+    for name in bench.ATTENTION_SOURCES:                          # a source changed since
+        (src_dir / name).write_bytes(b"B")
+        assert bench.measured_traffic(c4, None) is None, name
+        (src_dir / name).write_bytes(b"A of " + name.encode())
+        assert bench.measured_traffic(c4, None) == 121
+
+
+def test_traffic_record_is_keyed_on_every_source_of_the_attention_kernels():
+    """The files that define a kernel named in the table, and all they include."""
+    csrc = os.path.join(ROOT, "paper_2607_07724_amd", "csrc")
+    text = {n: open(os.path.join(csrc, n)).read() for n in os.listdir(csrc)}
+    want = {n for n in text if re.search(r"\battend(_keys)?_kernel\(AttnParams", text[n])}
+    assert want == {"attend.hip", "attend_keys.hip"}
+    while True:
+        more = {i for n in want for i in re.findall(r'#include "(\w+\.h)"', text[n]) if i in text} - want
+        if not more:
+            break
+        want |= more
+    assert set(bench.ATTENTION_SOURCES) == want
+
+
+def test_reported_kernel_is_the_one_launched():
+    from launch_probe import launches
+    for name, w in synth.WORKLOADS.items():
+        p = ugbs.Problem.make(w.B, w.H, w.Hkv, w.N, w.d, w.k, w.q, w.backbone, rho=w.rho)
+        (st, xs), = launches([("attend", p, p.W)])
+        assert st == 0 and [x["kernel"] for x in xs] == [bench.ATTENTION_KERNELS[name]], name
 
 
 def test_more_than_one_gpu_is_refused_with_a_message():
