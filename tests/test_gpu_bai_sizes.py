@@ -1,6 +1,7 @@
 """Diagnostics at the sizes where their kernels change form: rows on both
 sides of 512 and 1024 blocks, ranks on both sides of a group of eight, a
-partial group of heads, and head statistics over many tied tiles."""
+partial group of heads, and head statistics over many tied tiles and over
+NaN records."""
 import numpy as np
 import pytest
 
@@ -52,3 +53,27 @@ def test_heads_with_tied_tiles(T, q):
     gaps = {f: rec[f] for f in ("g", "G", "r", "sigma", "delta2")}
     gaps["valid"] = rec["valid"].astype(bool)
     compare_heads(hd, bai.head_stats(gaps, rec["fail_k"], rec["fail_rk"], tau32, q, k, n_s))
+
+
+@pytest.mark.parametrize("T", [40, 90])
+def test_heads_with_nan_records(T):
+    """NaN spacings and sigmas (infinite scores) rank above every number; the
+    tiles of NaN sigmas count among the routed ones besides the nq first."""
+    g = np.random.default_rng(50 + T)
+    n_s, q, nq = 16, 0.3, int(np.ceil(0.3 * T))
+    rec = np.zeros((1, 1, T), np.dtype(ugbs.BAI_TILE_FIELDS))
+    for f in ("g", "G", "r", "sigma", "delta2"):
+        rec[f] = g.random((1, 1, T)).astype(np.float32) + np.float32(0.5)
+    rec["sigma"][0, 0, [3, T // 2, T - 1]] = np.nan
+    rec["delta2"][0, 0, ::4] = np.nan
+    rec["fail_k"] = g.integers(0, n_s + 1, (1, 1, T))
+    rec["valid"] = 1
+    p = ugbs.Problem.make(1, 1, 1, 64 * T, 64, 4, q)
+    hd = gpu_heads(p, dev(rec.view(np.uint8).reshape(-1)), np.full((1, 1), 0.3, np.float32), n_s)
+    sig, d2, d = (rec[f][0, 0] for f in ("sigma", "delta2", "fail_k"))
+    order = np.argsort(sig, kind="stable")             # NaN last
+    assert hd["sigma_q"][0, 0] == np.float64(sig[order[nq - 1]])
+    assert hd["delta2_p05"][0, 0] == np.float64(np.sort(d2)[int(0.05 * (T - 1))])
+    assert hd["delta2_p50"][0, 0] == np.float64(np.sort(d2)[int(0.5 * (T - 1))])
+    top, routed = int(np.sort(d)[::-1][:nq].sum()), int(d[order[:nq]].sum() + d[np.isnan(sig)].sum())
+    assert hd["mc_regret"][0, 0] == (top / n_s - routed / n_s) / T
