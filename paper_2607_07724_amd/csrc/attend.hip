@@ -1,9 +1,9 @@
-// Stage 5 at d 256, and at d 128 where the walk is bound beyond the L2 (see
-// coupled_walk; attend_keys.hip: d 64 and the rest of d 128): block-sparse causal
-// attention over kv_idx, a bitmap, or an in-kernel selection (A.10; Eq. (Attn)).
+// Stage 5 at d 256, at d 128 where the walk is bound beyond the L2 (coupled_walk),
+// and at d 64 and 128 for few short lists (few_short_lists); attend_keys.hip: the
+// rest of d 64 and 128.  Block-sparse causal attention over kv_idx, a bitmap, or an in-kernel selection (A.10; Eq. (Attn)).
 //
 // One workgroup per (batch, query head, Q-tile) unit: four waves of 16 query
-// rows (d 128: two of 32); a wave owns its rows for every key of a block.  The
+// rows (d 64 and 128: two of 32); a wave owns its rows for every key of a block.  The
 // tile's kept blocks are first turned into an ascending list of distinct blocks
 // in 0..t (so the diagonal block comes last), then visited one by one.
 // (Splitting the keys over the waves instead, as attend_keys.hip does, needs all
@@ -41,9 +41,9 @@
 namespace ugbs {
 namespace {
 
-// Waves per unit and 16-row tiles per wave: d 128 runs two waves of 32 query
-// rows, d 256 four waves of 16 (half the accumulators per wave).  Two waves per
-// SIMD at both.
+// Waves per unit and 16-row tiles per wave: d 64 and 128 run two waves of 32
+// query rows, d 256 four waves of 16 (half the accumulators per wave).  Two waves
+// per SIMD at each.
 template <int D>
 struct Geo {
   static constexpr int RT = D > 128 ? 1 : 2;   // 16-row tiles per wave

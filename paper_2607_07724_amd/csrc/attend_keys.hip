@@ -15,8 +15,9 @@
 //   S^T = K Q^T   [32 keys x 64 rows]: K rows from LDS (ds_read_b128) are the
 //                 A operand, read once for all 64 rows; the query rows stay in
 //                 registers as the B operand (at d 128 the last 16 of them in
-//                 LDS: 252 registers, no spills); a lane ends up with 8 keys
-//                 of one row per 16-row tile;
+//                 LDS: 252 registers with two waves, 256 with four, no spills;
+//                 the in-kernel selection spills up to 8); a lane ends up with
+//                 8 keys of one row per 16-row tile;
 //   softmax       fp32, base 2; whether a reference maximum has to move is asked
 //                 per lane first, the cross-lane maximum only taken when one does;
 //   O^T += V^T P^T  a lane's probabilities, packed to bf16, already are the B
@@ -30,10 +31,11 @@
 // the other two phases to land.  With PV at a raised priority the two waves of
 // a SIMD settle on opposite phases.
 //
-// What bounds it: at d 128 the power limit (1.82 GHz; zeros in all inputs run
-// at 2.4 GHz) with the matrix cores 54% and the vector ALU 57% busy; the
-// 64-byte-per-clock staging path is as long as the matrix work (64 FLOP per
-// staged byte).  At d 64 the vector ALU (exponentials).  Measured against the
+// What bounds it: at d 128 the power limit and, right behind it, the loads.  128K,
+// 32/8 heads, k 64: 10.1 ms at 1.64 GHz, the matrix cores 53% busy, the vector ALU
+// issuing 52% of the time, the texture unit 69% busy; zeros in all inputs run at 2.39
+// GHz and take 9.4 ms.  (The 64-byte-per-clock staging path is as long as the matrix
+// work, 64 FLOP per staged byte, and 53 GB of it come from beyond the L2.)  At d 64 the vector ALU (exponentials).  Measured against the
 // form it replaced (both waves of a unit on all 64 keys and 32 rows each, two
 // workgroup barriers per block, twice the LDS reads): lists at d 128, 128K
 // (32/8 heads, k 64) 10.4 -> 9.8 ms, 64K (28/4) 4.34 -> 4.10, 32K (k 32) 1.13 ->

@@ -31,7 +31,8 @@
 // (b, h, t) holds the t-1 candidates 1..t-1).
 //
 // select_kernel: one wave per unit, heaviest tile first; compiled for five row
-// sizes, and slots past a row's end skipped in groups of eight.  Tile scores
+// sizes (each with and without the pre-filter), slots past a row's end skipped in
+// groups of eight.  Tile scores
 // become order-preserving 32-bit keys (-0 folded into +0).  A per-lane
 // top-3 pre-filter bounds the R-th largest key from below (R = min(max(W -
 // |F|, m + 1), |C|): the listed candidates, and at least the m + 1 that
@@ -41,9 +42,10 @@
 // index) and ordered by (key, ~index) with a bitonic sort: in registers
 // across lanes for R <= 128, in LDS above.  sigma uses IEEE fp32 subtract and
 // divide.  The kernel is bound by instruction issue, not by its reads: on
-// the 128K layer 1,620 VALU instructions per unit kept the SIMDs' VALU
-// issue 84% busy (0.20 ms; skipped groups and the three-operand median in the
-// pre-filter took 5% off scores and selection at 1021 blocks, 0.291 -> 0.275).  Splitting the stages keeps each kernel at its own
+// the 128K layer 1,400 VALU instructions per unit keep the SIMDs' VALU issue
+// 76% busy (0.173 ms; 1,620, 85% and 0.198 before skipped groups and the
+// three-operand median in the pre-filter, which took 5% off scores and selection
+// at 1021 blocks, 0.291 -> 0.275).  Splitting the stages keeps each kernel at its own
 // occupancy (the scoring kernel is bound by registers, the selection
 // kernel by instruction issue).
 #include "select_common.h"
@@ -475,8 +477,7 @@ score_kernel_q128x2(SelParams P) {
 }
 
 // K-mean d 128 tile scores: the body held to 96 registers, five waves per
-// SIMD instead of four (the 16 KiB ring allows it; a few values spill to
-// scratch): score + select 1.09 -> 0.99 ms on the 28/4-head d 128 layer at
+// SIMD instead of four (the 16 KiB ring allows it): score + select 1.09 -> 0.99 ms on the 28/4-head d 128 layer at
 // 128K, outputs bit-identical.  (K-mean d 256 held to three waves spills
 // 65 registers and runs 1.5x slower; it keeps two.)
 template <int OUT>
@@ -747,7 +748,7 @@ hipError_t launch_score(SelParams P, hipStream_t stream) {
   using MC = MetaChunk<D, QUEST>;
   P.ring_lds = MC::kRingSlots * MC::kBytes;
   const size_t smem = (size_t)P.ring_lds;
-  if (smem > 65536) {
+  if constexpr (MC::kRingSlots * MC::kBytes > 65536) {
     const hipError_t e = hipFuncSetAttribute((const void*)score_kernel<D, QUEST, OUT>,
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;

@@ -1,9 +1,10 @@
 """Attention with the keys of a unit split over two or four waves (d 64, 128).
 
 Four waves take over when the units are few (d 128: 512 and fewer, d 64: 768)
-and when there are a few rounds of units that visit many blocks; for bitmaps up
-to 1024 units of 96 and more blocks (d 64: 7680).  The parametrised shapes lie on
-both sides of those lines.  The lists are where the split can go wrong: single blocks (waves
+and when there are a few rounds of units with long chains; for bitmaps up to
+1024 units of 96 and more blocks (d 64: 7680).  Lists of at most four blocks take
+the kernel whose waves split the rows, up to 1024 units.  The parametrised
+shapes lie on both sides of those lines.  The lists are where the split can go wrong: single blocks (waves
 without an entry), the diagonal alone (a wave whose keys are all masked for
 half of the rows), rows without the diagonal, odd and even counts, empty
 rows (O = 0), widths past one 64-entry read.  A large logit scale makes the
