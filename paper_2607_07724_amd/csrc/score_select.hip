@@ -349,6 +349,9 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
         // the roughness mode keeps its registers for the row differences and
         // reads each column tile's operands at the tile's start
         constexpr bool EARLY = AHEAD && !ROUGH;
+        // matrix work ahead of other waves' max and stores, for every column tile; the
+        // operand reads with it where they alternate with it (K-mean d 128: 0.4%)
+        if constexpr (!AHEAD) __builtin_amdgcn_s_setprio(1);
         if constexpr (AHEAD) {
           read_b(0);
           __builtin_amdgcn_sched_barrier(0);   // keep the reads ahead of the matrix instructions
@@ -360,7 +363,7 @@ __device__ __forceinline__ void score_body(const SelParams& P) {
             if (ct > 0) read_b(ct);
             __builtin_amdgcn_sched_barrier(0);
           }
-          __builtin_amdgcn_s_setprio(1);   // matrix work ahead of other waves' max and stores
+          if (AHEAD || ct > 0) __builtin_amdgcn_s_setprio(1);
           f32x4 acc[RT];
 #pragma unroll
           for (int rt = 0; rt < RT; ++rt) acc[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
